@@ -43,7 +43,9 @@ TRAFFIC_FILES = (os.path.join(HERE, "profiles", "llama7b_generation_64x4096_hbm_
 # HIP sources each kernel family is built from (its traffic figure is void
 # once any of them changes)
 FAMILY_SOURCES = {
-    "gemm": ("gemm.hip", "common.h"), "kv_generate": ("gemm.hip", "kvgen.hip", "common.h"),
+    "gemm": ("gemm.hip", "gemm_tile.h", "gemm_mid.h", "gemm_mid.hip", "gemm_mid_128x128.hip",
+             "common.h"),
+    "kv_generate": ("gemm.hip", "gemm_tile.h", "kvgen.hip", "common.h"),
     "attention": ("attention.hip", "common.h"), "attention_decode": ("attention.hip", "common.h"),
     "exit_test": ("exit_test.hip", "common.h"),
     "compact_single": ("compact.hip", "common.h"),

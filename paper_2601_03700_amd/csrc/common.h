@@ -276,7 +276,8 @@ struct GemmArgs {
   int head_dim, d_q;
   void* q_out; void* k_cache; void* v_cache;   // caches already offset to the layer
   const char* name;       // timing label (string literal), nullable
-  // f32 workspace of the skinny path (M_max <= 64: decode), nullable; used
+  // f32 workspace of the skinny path (M_max <= 64: decode) and, above it, of
+  // tiles cut along K (mid_ws_bytes), nullable; skinny: used
   // when at least skinny_ws_bytes(N or 2N for SWIGLU, K) bytes
   float* skinny_ws; size_t skinny_ws_bytes;
   // grouped KV generation: per-layer bias stride, and A already in the
@@ -305,6 +306,8 @@ struct RowExit {
   double* sim_out;              // [M], nullable
 };
 size_t skinny_ws_bytes(int n_cols, int K);
+// workspace with which gemm() may cut tiles along K for up to M_max rows
+size_t mid_ws_bytes(int M_max, int N, int K, int epi);
 // whether gemm() runs g on the skinny path and can fill g.rinv_out / g.ln_out
 // or run g.exit
 bool gemm_skinny_row_norm(const GemmArgs& g);

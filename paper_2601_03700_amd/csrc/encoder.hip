@@ -151,6 +151,13 @@ EncWs carve(const adept_encoder_args* a, void* base) {
     w.skinny_bytes = std::max({skinny_ws_bytes(3 * dq, a->d_model), skinny_ws_bytes(a->d_model, dq),
                                skinny_ws_bytes(a->d_ff, a->d_model),
                                skinny_ws_bytes(a->d_model, a->d_ff)});
+  } else {
+    w.skinny_bytes = std::max({mid_ws_bytes(a->n_tok, 3 * dq, a->d_model, EPI_QKV),
+                               mid_ws_bytes(a->n_tok, a->d_model, dq, EPI_RESID),
+                               mid_ws_bytes(a->n_tok, a->d_ff, a->d_model, EPI_GELU),
+                               mid_ws_bytes(a->n_tok, a->d_model, a->d_ff, EPI_RESID)});
+  }
+  if (w.skinny_bytes) {
     w.skinny = (float*)(p + off);
     off += align256(w.skinny_bytes);
   }

@@ -32,7 +32,7 @@ struct LayerWs {
   int32_t* fsel;      // [n_tok]: fused schedule, 1 where a row's exit state is in h[layer & 1]
   void* prompt;   size_t prompt_bytes;   // per-sequence keys of the all-at-once variant
   void* hsm;      size_t hsm_bytes;      // mapper activations (when a mapper is given)
-  float* skinny;  size_t skinny_bytes;   // GEMM partial sums when n_tok <= 64 (decode)
+  float* skinny;  size_t skinny_bytes;   // GEMM partial sums (bf16)
   float* gemm_tmp;  // f32 path only
   void* xnorm;      // [n_tok][D] normalised rows (GPT2 family)
   size_t total;
@@ -67,6 +67,14 @@ LayerWs carve(const adept_layer_args* a, void* base) {
     w.skinny_bytes = std::max({skinny_ws_bytes(3 * dq, a->d_model), skinny_ws_bytes(a->d_model, dq),
                                skinny_ws_bytes(2 * a->d_ff, a->d_model),
                                skinny_ws_bytes(a->d_model, a->d_ff)});
+  } else if (a->dtype == ADEPT_BF16) {
+    const int fe = gpt2 ? EPI_GELU_TANH : EPI_SWIGLU;
+    w.skinny_bytes = std::max({mid_ws_bytes(a->n_tok, 3 * dq, a->d_model, EPI_QKV),
+                               mid_ws_bytes(a->n_tok, a->d_model, dq, EPI_RESID),
+                               mid_ws_bytes(a->n_tok, a->d_ff, a->d_model, fe),
+                               mid_ws_bytes(a->n_tok, a->d_model, a->d_ff, EPI_RESID)});
+  }
+  if (w.skinny_bytes) {
     w.skinny = (float*)(p + off);
     off += align256(w.skinny_bytes);
   }

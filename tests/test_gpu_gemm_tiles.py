@@ -1,0 +1,67 @@
+"""The GEMM tiles between the skinny path (at most 64 rows) and the 256-row
+tile: row counts at the edges of the 128-row tiles, column counts that leave
+ragged 128- and 256-column tiles, and K long enough that tiles are cut along
+it.  Whole layers with exits, each checked on the GPU's own inputs against the
+oracle (tests/layer_check.py: per element within max(2e-2, one bf16 ulp))."""
+import math
+import sys
+
+import numpy as np
+import pytest
+
+import adept_inputs as ai
+from oracle import adept_oracle as O
+from paper_2601_03700_amd import binding as B
+from paper_2601_03700_amd.model import DecoderModel, EncoderModel
+from tests import layer_check as LC
+
+pytestmark = pytest.mark.gpu
+
+# widths and K of 12 to 26 stages of 64: tiles are cut; N of 13 x 64 and 13 x 128 columns
+LLAMA = ai.DecoderShape(n_layers=2, d_model=768, n_heads=6, head_dim=128, d_ff=1664, vocab=384)
+GPT2 = ai.DecoderShape(n_layers=2, d_model=832, n_heads=13, head_dim=64, d_ff=1664, vocab=448,
+                       family="gpt2", max_pos=512)
+ENC = ai.EncoderShape(n_layers=2, d_model=768, n_heads=12, head_dim=64, d_ff=1600, vocab=500,
+                      max_pos=512)
+
+
+def say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.mark.parametrize("shape,rows", [(LLAMA, 65), (LLAMA, 128), (LLAMA, 129), (LLAMA, 257),
+                                        (LLAMA, 385), (GPT2, 65), (GPT2, 127), (GPT2, 300)])
+def test_decoder_rows(shape, rows):
+    say(f"gemm tiles {shape.family} rows={rows}")
+    make = ai.gpt2_weights if shape.family == "gpt2" else ai.decoder_weights
+    w32 = make(shape, seed=rows, dtype="bf16")
+    ids = ai.token_ids(rows, shape.vocab, 1, rows)
+    # a third of the rows leave after layer 1: layer 2 has fewer row tiles than
+    # the grid, and the K/V of those rows are generated
+    force = (np.random.default_rng(rows).random(ids.shape) < 0.34).astype(np.int32)
+    model = DecoderModel(shape, w32, dtype="bf16", rope_max_pos=512)
+    rep = LC.Report(say)
+    chk = LC.DecoderLayerCheck(O.as64(w32), shape, None, O.ExitConfig(delta=math.inf), "bf16",
+                               force_layer=force, report=rep)
+    chk.cache = model.new_cache(1, rows)
+    res, _ = model.prefill(ids, B.exit_cfg(math.inf, shape.n_layers), force_layer=force,
+                           cache=chk.cache, on_layer=chk)
+    chk.finish(res.state, res.logits, res.rows)
+    rep.summary()
+
+
+@pytest.mark.parametrize("rows", [70, 128, 300])
+def test_encoder_rows(rows):
+    say(f"gemm tiles encoder rows={rows}")
+    w32 = ai.encoder_weights(ENC, seed=rows, dtype="bf16")
+    ids = ai.token_ids(rows, ENC.vocab, 1, rows)
+    force = (np.random.default_rng(rows).random(ids.shape) < 0.34).astype(np.int32)
+    force[:, 0] = 0
+    rep = LC.Report(say)
+    chk = LC.EncoderLayerCheck(O.as64(w32), ENC, O.ExitConfig(delta=math.inf), force_layer=force,
+                               report=rep, stop_at_cls=True)
+    out = EncoderModel(ENC, w32).classify(ids, B.exit_cfg(math.inf, ENC.n_layers),
+                                          force_layer=force, on_layer=chk)
+    chk.finish(out, rows)
+    rep.summary()
