@@ -15,8 +15,9 @@ struct Tile {
   int cols, slots;
   double fixed;
 };
-constexpr Tile kTileA{128, 512, 3.0}, kTileB{256, 256, 6.0};
-constexpr double kLargeStage = 1.25, kLargeFixed = 10.0;   // 256x256, 256 slots
+constexpr Tile kTileA{128, 512, 3.0}, kTileB{256, 256, 6.5};
+constexpr double kLargeStage = 1.25, kLargeFixed = 18.0;   // 256x256, 256 slots
+constexpr double kLargeGelu = 10.0;      // its GELU epilogues, over 4 blocks a wave
 constexpr double kReduceUs = 4.0;        // the second kernel
 constexpr double kPartBytesUs = 6.0e6;   // bytes per us the partial sums are written and read at
 
@@ -24,7 +25,7 @@ double stage_us(const Tile& c, int w, int tm) {
   const double f = w / 256.0;
   const double hbm = 0.5 + 0.4 * std::min(1.0, (double)w / tm * c.cols / 16384.0);
   const double t = c.cols == 256 ? 0.62 + 0.31 * f * f
-                                 : (w <= 256 ? 0.50 + 0.04 * f : 0.84 + 0.19 * (f - 1.0));
+                                 : (w <= 256 ? 0.50 + 0.04 * f : 0.88 + 0.18 * (f - 1.0));
   return std::max(t, hbm);
 }
 
@@ -106,7 +107,8 @@ MidTile mid_choose(const GP& p, int epi, size_t ws_bytes) {
   const int KT = p.K / BK, tm = ceil_div(p.M_max, kMidRows);
   int tail, S;
   const int tl = ceil_div(p.M_max, 256) * mid_tiles_n(256, p.N, epi);
-  double best = ceil_div(tl, 256) * (kLargeFixed + kLargeStage * KT);
+  const bool gelu = epi == EPI_GELU || epi == EPI_GELU_TANH;
+  double best = ceil_div(tl, 256) * (kLargeFixed + (gelu ? kLargeGelu : 0.0) + kLargeStage * KT);
   MidTile pick = kTileLarge;
   const bool split = ws_bytes > 0 && ws_bytes >= mid_ws_bytes(p.M_max, p.N, p.K, epi);
   const double b = best_plan(kTileB, tm, mid_tiles_n(256, p.N, epi), KT, split, &tail, &S);
