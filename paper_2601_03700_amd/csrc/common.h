@@ -87,6 +87,10 @@ __device__ __forceinline__ bool exit_decision(bool pass, int layer, int min_exit
 // access is a 16-byte vector.  Mean and variance in f32 from the registers
 // (two passes); o = (x - mean) / sqrt(var + eps) [* gain + bias].  o may be x.
 template <int R>
+__device__ __forceinline__ void layernorm_regs(float (&v)[R][8], float s, int d, float eps,
+                                               const bf16* __restrict__ gain,
+                                               const bf16* __restrict__ bias, bf16* o, int lane);
+template <int R>
 __device__ __forceinline__ void layernorm_row_vec(const bf16* x, int d, float eps,
                                                   const bf16* __restrict__ gain,
                                                   const bf16* __restrict__ bias, bf16* o,
@@ -106,6 +110,14 @@ __device__ __forceinline__ void layernorm_row_vec(const bf16* x, int d, float ep
       s += v[j][2 * e] + v[j][2 * e + 1];
     }
   }
+  layernorm_regs<R>(v, s, d, eps, gain, bias, o, lane);
+}
+
+// The rest of it: the row in registers (zeros past d), s the lane's sum.
+template <int R>
+__device__ __forceinline__ void layernorm_regs(float (&v)[R][8], float s, int d, float eps,
+                                               const bf16* __restrict__ gain,
+                                               const bf16* __restrict__ bias, bf16* o, int lane) {
   const float mean = wave_sum_f32(s) / (float)d;
   float q = 0.0f;
 #pragma unroll

@@ -84,6 +84,26 @@ __global__ void embed_positions_kernel(int n, int d, int vocab, int max_pos,
   st(out + idx, ld(wte + id * d + c) + ld(wpe + p * d + c));
 }
 
+// The same in bf16 by 16-byte chunks, cpr per row.
+__global__ __launch_bounds__(256) void embed_positions_vec_kernel(
+    uint32_t total, uint32_t cpr, int vocab, int max_pos, const int32_t* __restrict__ ids,
+    const int32_t* __restrict__ pos, const uint4* __restrict__ wte, const uint4* __restrict__ wpe,
+    uint4* __restrict__ out) {
+  const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
+  if (idx >= total) return;
+  const uint32_t k = idx / cpr, c = idx - k * cpr;
+  const int64_t id = min(max(ids[k], 0), vocab - 1);
+  const int64_t p = min(max(pos[k], 0), max_pos - 1);
+  const uint4 a = wte[id * cpr + c], b = wpe[p * cpr + c];
+  const uint32_t u[4] = {a.x, a.y, a.z, a.w}, v[4] = {b.x, b.y, b.z, b.w};
+  uint32_t y[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    y[e] = pack_bf16x2(__uint_as_float(u[e] << 16) + __uint_as_float(v[e] << 16),
+                       __uint_as_float(u[e] & 0xffff0000u) + __uint_as_float(v[e] & 0xffff0000u));
+  out[idx] = make_uint4(y[0], y[1], y[2], y[3]);
+}
+
 // bias[l][o] += sum_c w[l][o][c] * shift[l][c]: one wave per (l, o), the
 // dot product in f32, rounded once into the bias.
 template <typename T>
@@ -175,6 +195,14 @@ extern "C" adept_status adept_embed_positions(adept_dtype dt, int n, int d_model
   ADEPT_REQUIRE(ids && pos && wte && wpe && h0, "embed_positions: NULL tensor");
   if (n == 0) return ADEPT_OK;
   const int64_t total = (int64_t)n * d_model;
+  if (dt == ADEPT_BF16 && d_model % 8 == 0 && total / 8 < (1ll << 31) && aligned16(wte) &&
+      aligned16(wpe) && aligned16(h0)) {
+    const uint32_t chunks = (uint32_t)(total / 8);
+    ADEPT_LAUNCH(embed_positions_vec_kernel, dim3(ceil_div(chunks, 256)), dim3(256), 0,
+                 as_stream(stream), chunks, (uint32_t)(d_model / 8), vocab, max_pos, ids, pos,
+                 (const uint4*)wte, (const uint4*)wpe, (uint4*)h0);
+    return launch_status("embed_positions");
+  }
   dim3 grid((unsigned)((total + 255) / 256));
   if (dt == ADEPT_BF16)
     ADEPT_LAUNCH(embed_positions_kernel<bf16>, grid, dim3(256), 0, as_stream(stream), n,
