@@ -304,6 +304,9 @@ struct GemmArgs {
   // bf16 values); nullable.  Or exit (nullable): the GLOBAL exit test of
   // each result row (as adept_exit_test: flags, similarities, inertia update).
   float* rinv_out; void* ln_out; float row_eps;
+  // f32 only, where gemm_f32_fused holds: scale row m by 1/sqrt(mean(a^2) +
+  // row_eps) of its A row (formed by the GEMM) instead of row_scale
+  bool row_norm;
   const struct RowExit* exit;
 };
 // The GLOBAL-metric exit test (Eq. 7-8) run by a residual epilogue over its
@@ -335,7 +338,15 @@ adept_status attend_dispatch(adept_dtype dt, int n_heads, int head_dim, float sc
                              const int32_t* key_len, const uint8_t* key_live, void* out,
                              void* workspace, size_t workspace_bytes, bool allow_tiles,
                              hipStream_t s);
+// whether gemm_f32 / gemm_f32_direct run g as one kernel (then tmp is unused
+// and row_norm is allowed)
+bool gemm_f32_fused(const GemmArgs& g);
 adept_status gemm_f32(const GemmArgs& g, float* tmp, hipStream_t s);      // f32 + epilogue
+// f32 KV generation on the same kernel (rows g.rows, factors from g.row_eps);
+// *ran = false where its loads or heads do not fit (nothing enqueued)
+adept_status kvgen_f32_fused(const GemmArgs& g, int n_layers, const int32_t* exit_layer,
+                             const float* gain, int64_t b_layer_stride,
+                             int64_t cache_layer_stride, bool* ran, hipStream_t s);
 adept_status gemm_f32_direct(const GemmArgs& g, hipStream_t s);           // f32, C = A B^T
 adept_status gemm_kv_grouped(const GemmArgs& g, const int32_t* work, const int32_t* n_work,
                              int max_work, const int32_t* grp_m,

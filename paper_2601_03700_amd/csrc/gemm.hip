@@ -14,9 +14,6 @@
 // the device from the exited rows sorted by exit layer (rows with i* < r form
 // a prefix); B is [Wk_r; Wv_r] with layer r's gain folded in, the row scale is
 // 1/rms(s~), and the epilogue writes K (with RoPE) and V into cache[r].
-//
-// f32 path (small configurations only): a plain 64x64-tiled FMA GEMM into a
-// float scratch buffer followed by an element-wise epilogue kernel.
 #include <algorithm>
 
 #include "gemm_tile.h"
@@ -75,99 +72,6 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_kv_flat_kernel(GP p) {
   gemm_tile<EPI_KV, true, HD, EXT, GeoL, false>(p, smem, layer, mt, nt, p.grp_m[layer],
                                                p.B + (int64_t)(layer - 1) * p.b_layer_stride, 0,
                                                p.K / BK, nullptr);
-}
-
-// ----------------------------------------------------------------------------
-// f32 path
-// ----------------------------------------------------------------------------
-constexpr int FT = 64, FK = 16;
-
-__global__ __launch_bounds__(256) void gemm_f32_kernel(int M_max, const int32_t* M_dev, int N,
-                                                       int K, const float* __restrict__ A,
-                                                       const int32_t* __restrict__ a_rows,
-                                                       int64_t lda, const float* __restrict__ B,
-                                                       int64_t ldb, float* __restrict__ C,
-                                                       int64_t ldc) {
-  __shared__ float sA[FK][FT + 1];
-  __shared__ float sB[FK][FT + 1];
-  const int M = M_dev ? min(*M_dev, M_max) : M_max;
-  const int m0 = blockIdx.x * FT, n0 = blockIdx.y * FT;
-  if (m0 >= M) return;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += FK) {
-    for (int e = threadIdx.x; e < FT * FK; e += 256) {
-      const int r = e / FK, c = e % FK;
-      int m = m0 + r;
-      if (m >= M) m = m0;
-      const int arow = a_rows ? a_rows[m] : m;
-      sA[c][r] = (k0 + c < K) ? A[(int64_t)arow * lda + k0 + c] : 0.0f;
-      const int n = n0 + r;
-      sB[c][r] = (n < N && k0 + c < K) ? B[(int64_t)n * ldb + k0 + c] : 0.0f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < FK; ++c) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = sA[c][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = sB[c][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty * 4 + i;
-    if (m >= M) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx * 4 + j;
-      if (n < N) C[(int64_t)m * ldc + n] = acc[i][j];
-    }
-  }
-}
-
-// Element-wise epilogue over the f32 scratch T[m][n] (n < n_out), after the
-// per-row scale.
-__global__ void epilogue_f32_kernel(int epi, int M_max, const int32_t* M_dev, int n_out,
-                                    const float* __restrict__ T, int64_t ldt, GP p) {
-  const int M = M_dev ? min(*M_dev, M_max) : M_max;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int m = (int)(idx / n_out), n = (int)(idx % n_out);
-  if (m >= M) return;
-  const float sc = p.row_scale ? p.row_scale[m] : 1.0f;
-  const float* t = T + (int64_t)m * ldt;
-  float* C = reinterpret_cast<float*>(p.C);
-  if (epi == EPI_STORE) {
-    C[(int64_t)m * p.ldc + n] = t[n] * sc;
-  } else if (epi == EPI_RESID) {
-    const int64_t row = p.rows[m];
-    C[row * p.ldc + n] = reinterpret_cast<const float*>(p.resid)[row * p.ldc + n] + t[n] * sc;
-  } else if (epi == EPI_SWIGLU) {
-    C[(int64_t)m * p.ldc + n] = silu(t[n] * sc) * (t[p.N + n] * sc);
-  } else {  // EPI_QKV
-    const int sec = n / p.d_q, cin = n - sec * p.d_q;
-    const int row = p.rows[m];
-    float* dst;
-    if (sec == 0) dst = reinterpret_cast<float*>(p.q_out) + (int64_t)m * p.d_q;
-    else dst = reinterpret_cast<float*>(sec == 1 ? p.k_cache : p.v_cache) + (int64_t)p.slot[row] * p.d_q;
-    if (sec == 2) {
-      dst[cin] = t[n] * sc;
-    } else {
-      const int hd = p.head_dim, half = hd / 2;
-      const int c = cin % hd, kk = c % half;
-      const int ps = p.pos[row];
-      const float cs = p.rope_cos[(int64_t)ps * half + kk], sn = p.rope_sin[(int64_t)ps * half + kk];
-      const float x = t[n] * sc;
-      const float y = (c < half ? t[n + half] : t[n - half]) * sc;
-      dst[cin] = c < half ? x * cs - y * sn : x * cs + y * sn;
-    }
-  }
 }
 
 // Sets a kernel's dynamic-LDS limit once per process.
@@ -528,24 +432,6 @@ adept_status launch_skinny(const GP& p, int Nt, int nout, hipStream_t s, const c
   return launch_status("skinny_epilogue");
 }
 
-GP to_gp(const GemmArgs& g) {
-  GP p{};
-  p.M_max = g.M_max; p.M_dev = g.M_dev; p.N = g.N; p.K = g.K;
-  p.A = (const bf16*)g.A; p.a_rows = g.a_rows; p.lda = g.lda;
-  p.B = (const bf16*)g.B; p.B2 = (const bf16*)g.B2; p.ldb = g.ldb;
-  p.C = g.C; p.ldc = g.ldc; p.c_f32 = g.c_f32; p.row_scale = g.row_scale;
-  p.rows = g.rows; p.resid = (const bf16*)g.resid; p.pos = g.pos; p.slot = g.slot;
-  p.bias = (const bf16*)g.bias;
-  p.rope_cos = g.rope_cos; p.rope_sin = g.rope_sin; p.head_dim = g.head_dim; p.d_q = g.d_q;
-  p.q_out = (bf16*)g.q_out; p.k_cache = (bf16*)g.k_cache; p.v_cache = (bf16*)g.v_cache;
-  p.bias_layer_stride = g.bias_layer_stride; p.a_sorted = g.a_sorted;
-  p.A2 = (const bf16*)g.A2; p.a_sel = g.a_sel;
-  p.rinv_out = g.rinv_out; p.ln_out = (bf16*)g.ln_out; p.row_eps = g.row_eps;
-  p.has_exit = g.exit != nullptr;
-  if (g.exit) p.ex = *g.exit;
-  return p;
-}
-
 bool aligned8(const void* p) { return ((uintptr_t)p & 7u) == 0; }
 
 bool aligned_operands(const GemmArgs& g) {
@@ -642,37 +528,6 @@ adept_status gemm(adept_dtype dt, const GemmArgs& g, hipStream_t s) {
     case EPI_GELU_TANH: return launch_bf16<EPI_GELU_TANH, 0>(p, s, g.name);
     default: set_error("gemm: bad epilogue"); return ADEPT_E_INVALID;
   }
-}
-
-// f32 GEMM + element-wise epilogue; tmp holds M_max x (N or 2N for SWIGLU) floats.
-adept_status gemm_f32(const GemmArgs& g, float* tmp, hipStream_t s) {
-  if (g.M_max <= 0) return ADEPT_OK;
-  const int nt = g.epi == EPI_SWIGLU ? 2 * g.N : g.N;
-  dim3 block(256);
-  dim3 grid(ceil_div(g.M_max, FT), ceil_div(g.N, FT));
-  ADEPT_LAUNCH(gemm_f32_kernel, grid, block, 0, s, g.M_max, g.M_dev, g.N, g.K,
-               (const float*)g.A, g.a_rows, g.lda, (const float*)g.B, g.ldb, tmp, (int64_t)nt);
-  ADEPT_CHECK_LAUNCH("gemm_f32");
-  if (g.epi == EPI_SWIGLU) {
-    ADEPT_LAUNCH(gemm_f32_kernel, grid, block, 0, s, g.M_max, g.M_dev, g.N, g.K,
-                 (const float*)g.A, g.a_rows, g.lda, (const float*)g.B2, g.ldb, tmp + g.N,
-                 (int64_t)nt);
-    ADEPT_CHECK_LAUNCH("gemm_f32");
-  }
-  GP p = to_gp(g);
-  const int64_t total = (int64_t)g.M_max * g.N;
-  ADEPT_LAUNCH(epilogue_f32_kernel, dim3((unsigned)((total + 255) / 256)), block, 0, s, g.epi,
-               g.M_max, g.M_dev, g.N, (const float*)tmp, (int64_t)nt, p);
-  return launch_status("epilogue_f32");
-}
-
-// f32 GEMM written straight to C (no epilogue, no row scale): C[m][n] = A[m] . B[n].
-adept_status gemm_f32_direct(const GemmArgs& g, hipStream_t s) {
-  if (g.M_max <= 0) return ADEPT_OK;
-  dim3 grid(ceil_div(g.M_max, FT), ceil_div(g.N, FT));
-  ADEPT_LAUNCH(gemm_f32_kernel, grid, dim3(256), 0, s, g.M_max, g.M_dev, g.N, g.K,
-               (const float*)g.A, g.a_rows, g.lda, (const float*)g.B, g.ldb, (float*)g.C, g.ldc);
-  return launch_status("gemm_f32");
 }
 
 // Grouped bf16 GEMM of the KV generation (see the header comment).  g.row_scale

@@ -999,6 +999,24 @@ __device__ __forceinline__ void raster_tile(int t, int tiles_m, int tiles_n, int
   *nt = r / rows_in_g;
 }
 
+inline GP to_gp(const GemmArgs& g) {
+  GP p{};
+  p.M_max = g.M_max; p.M_dev = g.M_dev; p.N = g.N; p.K = g.K;
+  p.A = (const bf16*)g.A; p.a_rows = g.a_rows; p.lda = g.lda;
+  p.B = (const bf16*)g.B; p.B2 = (const bf16*)g.B2; p.ldb = g.ldb;
+  p.C = g.C; p.ldc = g.ldc; p.c_f32 = g.c_f32; p.row_scale = g.row_scale;
+  p.rows = g.rows; p.resid = (const bf16*)g.resid; p.pos = g.pos; p.slot = g.slot;
+  p.bias = (const bf16*)g.bias;
+  p.rope_cos = g.rope_cos; p.rope_sin = g.rope_sin; p.head_dim = g.head_dim; p.d_q = g.d_q;
+  p.q_out = (bf16*)g.q_out; p.k_cache = (bf16*)g.k_cache; p.v_cache = (bf16*)g.v_cache;
+  p.bias_layer_stride = g.bias_layer_stride; p.a_sorted = g.a_sorted;
+  p.A2 = (const bf16*)g.A2; p.a_sel = g.a_sel;
+  p.rinv_out = g.rinv_out; p.ln_out = (bf16*)g.ln_out; p.row_eps = g.row_eps;
+  p.has_exit = g.exit != nullptr;
+  if (g.exit) p.ex = *g.exit;
+  return p;
+}
+
 // The extended instantiation only where the shape or the inputs need it.
 inline bool tile_needs_ext(const GP& p, int epi, int tile) {
   return (epi != EPI_SWIGLU && p.N % tile != 0) ||

@@ -10,8 +10,10 @@
 // row factor 1/rms(s) scales the accumulators; RoPE on K in the epilogue,
 // K/V stored straight into cache[r][slot].
 //
-// f32 (small configurations): one workgroup per (row, layer) pair computes
-// the normalised state in LDS and the 2*H*hd dot products directly.
+// f32 (small configurations): gemm_f32.hip's kernel over (16 rows, column
+// pair, layer); where its loads do not fit, one workgroup per (row, layer)
+// pair computes the normalised state in LDS and the 2*H*hd dot products
+// directly.
 //
 // adept_kv_generate_noalloc runs the same kernels with their scratch in a
 // file-scope device array instead of a caller workspace.
@@ -200,6 +202,16 @@ extern "C" adept_status adept_kv_generate(adept_dtype dt, int n_layers, int d_mo
   const int64_t layer_stride = n_slots * dq;
   if (dt == ADEPT_F32) {
     ADEPT_REQUIRE(d_model <= 8192 && dq <= 8192, "kv_generate: f32 path limited to width 8192");
+    GemmArgs g{};
+    g.M_max = max_rows; g.M_dev = n_rows; g.N = 2 * dq; g.K = d_model;
+    g.A = s_map; g.a_rows = rows; g.rows = rows; g.lda = d_model; g.B = w_kv; g.ldb = d_model;
+    g.epi = EPI_KV; g.pos = pos; g.slot = cache_slot; g.row_eps = eps;
+    g.rope_cos = rope_cos; g.rope_sin = rope_sin; g.head_dim = head_dim; g.d_q = dq;
+    g.k_cache = k_cache; g.v_cache = v_cache;
+    bool ran = false;
+    ADEPT_TRY(kvgen_f32_fused(g, n_layers, exit_layer, (const float*)attn_gain, w_kv_layer_stride,
+                              layer_stride, &ran, s));
+    if (ran) return ADEPT_OK;
     const size_t smem = (size_t)(d_model + dq) * sizeof(float);
     ADEPT_LAUNCH(kvgen_f32_kernel, dim3(max_rows, n_layers), dim3(256), smem, s, n_layers,
                        d_model, n_heads, head_dim, eps, (const float*)s_map, rows, n_rows,

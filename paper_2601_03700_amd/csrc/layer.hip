@@ -419,11 +419,13 @@ extern "C" adept_status adept_layer_step(const adept_layer_args* a, int layer, v
     ADEPT_TRY(exit_in_epilogue(gd));
     ADEPT_TRY(gemm(dt, gd, s));
   } else if (qmax > 0) {
+    // the f32 GEMM forms the row factors itself
+    auto norm_in_gemm = [&](GemmArgs& x) {
+      x.row_eps = a->rms_eps;
+      return dt == ADEPT_F32 && gemm_f32_fused(x);
+    };
     // 1. pre-attention RMSNorm: the gain is folded into W_qkv, the row factor
     //    1/rms(h) scales the GEMM accumulators
-    if (!rinv_fused)
-      ADEPT_TRY(row_rinv_sel(dt, D, a->rms_eps, a->h[in], a->h[out], fused ? ws.fsel : nullptr,
-                             qrows, nq, qmax, ws.rinv, s));
     // 2. Q/K/V projections of the gathered rows, RoPE, own K/V into cache[layer]
     GemmArgs g{};
     g.M_max = qmax; g.M_dev = nq; g.N = 3 * dq; g.K = D;
@@ -434,6 +436,11 @@ extern "C" adept_status adept_layer_step(const adept_layer_args* a, int layer, v
     g.rope_cos = a->rope_cos; g.rope_sin = a->rope_sin; g.head_dim = hd; g.d_q = dq;
     g.q_out = a->q_buf; g.k_cache = kc; g.v_cache = vc; g.name = "gemm_qkv";
     g.skinny_ws = ws.skinny; g.skinny_ws_bytes = ws.skinny_bytes;
+    if (norm_in_gemm(g))
+      g.row_norm = true;
+    else if (!rinv_fused)
+      ADEPT_TRY(row_rinv_sel(dt, D, a->rms_eps, a->h[in], a->h[out], fused ? ws.fsel : nullptr,
+                             qrows, nq, qmax, ws.rinv, s));
     ADEPT_TRY(run_gemm(dt, g, ws.gemm_tmp, s));
     // 3. attention over the mixed cache
     ADEPT_TRY(attend_dispatch(dt, H, hd, 1.0f / sqrtf((float)hd), 1, a->q_buf, act, nact, maxn,
@@ -452,7 +459,6 @@ extern "C" adept_status adept_layer_step(const adept_layer_args* a, int layer, v
       go.row_eps = a->rms_eps;
     }
     ADEPT_TRY(run_gemm(dt, go, ws.gemm_tmp, s));
-    if (!go.rinv_out) ADEPT_TRY(row_rinv(dt, D, a->rms_eps, a->h[out], act, nact, maxn, ws.rinv, s));
     // 6. gate/up projections with SwiGLU
     GemmArgs gu{};
     gu.M_max = maxn; gu.M_dev = nact; gu.N = F; gu.K = D;
@@ -460,6 +466,10 @@ extern "C" adept_status adept_layer_step(const adept_layer_args* a, int layer, v
     gu.epi = EPI_SWIGLU; gu.row_scale = ws.rinv;
     gu.C = a->ffn_act; gu.ldc = F; gu.name = "gemm_gate_up";
     gu.skinny_ws = ws.skinny; gu.skinny_ws_bytes = ws.skinny_bytes;
+    if (norm_in_gemm(gu))
+      gu.row_norm = true;
+    else if (!go.rinv_out)
+      ADEPT_TRY(row_rinv(dt, D, a->rms_eps, a->h[out], act, nact, maxn, ws.rinv, s));
     ADEPT_TRY(run_gemm(dt, gu, ws.gemm_tmp, s));
     // 7. down projection + residual (in place on h[out])
     GemmArgs gd{};
