@@ -304,9 +304,14 @@ struct GemmArgs {
   // bf16 values); nullable.  Or exit (nullable): the GLOBAL exit test of
   // each result row (as adept_exit_test: flags, similarities, inertia update).
   float* rinv_out; void* ln_out; float row_eps;
-  // f32 only, where gemm_f32_fused holds: scale row m by 1/sqrt(mean(a^2) +
-  // row_eps) of its A row (formed by the GEMM) instead of row_scale
+  // where gemm_f32_fused (f32) or gemm_direct_fits (bf16) holds: scale row m by
+  // 1/sqrt(mean(a^2) + row_eps) of its A row (formed by the GEMM) instead of
+  // row_scale
   bool row_norm;
+  // bf16, where gemm_direct_fits holds: the GEMM makes its own row list (then
+  // M_dev is the active count, A / A2 are read by token row) or clears a ticket;
+  // nullable
+  const struct RowList* list;
   const struct RowExit* exit;
 };
 // The GLOBAL-metric exit test (Eq. 7-8) run by a residual epilogue over its
@@ -320,6 +325,22 @@ struct RowExit {
   uint8_t* exit_flag;           // [M]
   double* sim_out;              // [M], nullable
 };
+// Row list of the fused decode schedule, formed by the GEMM itself (n_tok <=
+// 64): the active rows act[0 .. min(*M_dev, max_act)) followed by the rows that
+// exited at a layer below `layer` (ascending); an exited row's state is in A2
+// when its exit layer is of the other parity than layer - 1.  exit_layer NULL:
+// no list, only the ticket.  ticket (nullable): two words that are cleared.
+struct RowList {
+  int n_tok, layer, max_act;
+  const int32_t* exit_layer;
+  const int32_t* act;
+  unsigned long long* ticket;
+};
+constexpr int kDirectRows = 64;
+// whether gemm() runs g as one kernel without a workspace (gemm_direct.hip)
+bool gemm_direct_fits(int M_max, int n_weights, int K, int epi);
+bool gemm_direct_fits(const GemmArgs& g);
+adept_status gemm_direct(const GemmArgs& g, hipStream_t s);   // g checked by gemm()
 size_t skinny_ws_bytes(int n_cols, int K);
 // workspace with which gemm() may cut tiles along K for up to M_max rows
 size_t mid_ws_bytes(int M_max, int N, int K, int epi);
@@ -328,6 +349,33 @@ size_t mid_ws_bytes(int M_max, int N, int K, int epi);
 bool gemm_skinny_row_norm(const GemmArgs& g);
 
 adept_status gemm(adept_dtype dt, const GemmArgs& g, hipStream_t s);       // bf16 MFMA path
+// The GLOBAL exit test and the list update of at most 64 bf16 rows as one
+// kernel (csrc/exit_test.hip), for an encoder layer with the LayerNorm before
+// (ln_g), the early stop (cls_seq_len > 0) and the dead keys (key_live).
+struct ExitCompact {
+  int d, layer, max_active;
+  const adept_exit_cfg* cfg;
+  const int32_t *rows, *n_active;
+  void* h;                      // layer output by token row
+  float* inertia;
+  const int32_t* force_layer;
+  uint8_t* exit_flag;
+  double* sim_out;
+  int32_t *next, *n_next, *exited, *n_exited, *exit_layer;
+  unsigned long long* ticket;   // two zeroed words (GemmArgs::list clears them)
+  const void *ln_g, *ln_b;
+  float ln_eps;
+  int cls_seq_len;
+  uint8_t* key_live;
+};
+bool exit_compact_fits(const adept_exit_cfg& cfg, int d, int max_active);
+adept_status exit_compact(const ExitCompact& x, hipStream_t s);
+// the argument checks of adept_compact
+adept_status compact_check(int layer, int n_layers, const uint8_t* exit_flag,
+                           const int32_t* active_rows, const int32_t* n_active,
+                           const int32_t* next_rows, const int32_t* n_next,
+                           const int32_t* exited_rows, const int32_t* n_exited,
+                           const int32_t* exit_layer);
 // attention (csrc/attention.hip): adept_attend with a switch that can forbid
 // the query-tile kernel (one query per sequence: decode)
 size_t attend_workspace_bytes(int max_active, int n_seq, int n_heads, int head_dim, int s_max);

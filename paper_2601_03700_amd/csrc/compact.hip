@@ -316,6 +316,23 @@ __global__ __launch_bounds__(kThreads) void compact_scatter(
 }
 
 }  // namespace
+
+adept_status compact_check(int layer, int n_layers, const uint8_t* exit_flag,
+                           const int32_t* active_rows, const int32_t* n_active,
+                           const int32_t* next_rows, const int32_t* n_next,
+                           const int32_t* exited_rows, const int32_t* n_exited,
+                           const int32_t* exit_layer) {
+  ADEPT_REQUIRE(layer >= 1 && layer <= n_layers, "compact: layer %d outside 1..%d", layer, n_layers);
+  ADEPT_REQUIRE(exit_flag && active_rows && n_active && next_rows && n_next && exited_rows &&
+                    n_exited && exit_layer,
+                "compact: NULL tensor");
+  ADEPT_REQUIRE(aligned16(active_rows) && ((uintptr_t)exit_flag & 3) == 0,
+                "compact: active_rows must be 16-byte and exit_flag 4-byte aligned");
+  ADEPT_REQUIRE(next_rows != active_rows && exited_rows != active_rows,
+                "compact: outputs must not alias active_rows");
+  return ADEPT_OK;
+}
+
 }  // namespace adept
 using namespace adept;
 
@@ -334,14 +351,8 @@ extern "C" adept_status adept_compact(int layer, int n_layers, const uint8_t* ex
                                       int32_t* exit_layer, void* workspace,
                                       size_t workspace_bytes, void* stream) {
   ADEPT_REQUIRE(max_active >= 0, "compact: max_active < 0");
-  ADEPT_REQUIRE(layer >= 1 && layer <= n_layers, "compact: layer %d outside 1..%d", layer, n_layers);
-  ADEPT_REQUIRE(exit_flag && active_rows && n_active && next_rows && n_next && exited_rows &&
-                    n_exited && exit_layer,
-                "compact: NULL tensor");
-  ADEPT_REQUIRE(aligned16(active_rows) && ((uintptr_t)exit_flag & 3) == 0,
-                "compact: active_rows must be 16-byte and exit_flag 4-byte aligned");
-  ADEPT_REQUIRE(next_rows != active_rows && exited_rows != active_rows,
-                "compact: outputs must not alias active_rows");
+  ADEPT_TRY(compact_check(layer, n_layers, exit_flag, active_rows, n_active, next_rows, n_next,
+                          exited_rows, n_exited, exit_layer));
   hipStream_t s = as_stream(stream);
   if (max_active <= kSingleMax) {
     ADEPT_LAUNCH(compact_single, dim3(1), dim3(kThreads), 0, s, layer, exit_flag,

@@ -175,9 +175,17 @@ adept_status layernorm_rows(int d, float eps, const void* x, const int32_t* rows
 struct EncWs {
   void* compact; size_t compact_bytes;
   void* attend;  size_t attend_bytes;
-  float* skinny; size_t skinny_bytes;
+  float* parts;  size_t parts_bytes;   // GEMM partial sums
+  unsigned long long* ticket;          // two words of exit_compact (step_direct)
   size_t total;
 };
+
+// Whether all GEMMs of the step run as one kernel each (gemm_direct.hip)
+bool step_direct(const adept_encoder_args* a) {
+  const int dq = a->n_heads * a->head_dim, D = a->d_model, F = a->d_ff, n = a->n_tok;
+  return gemm_direct_fits(n, 3 * dq, D, EPI_QKV) && gemm_direct_fits(n, D, dq, EPI_RESID) &&
+         gemm_direct_fits(n, F, D, EPI_GELU) && gemm_direct_fits(n, D, F, EPI_RESID);
+}
 
 EncWs carve(const adept_encoder_args* a, void* base) {
   EncWs w{};
@@ -188,19 +196,22 @@ EncWs carve(const adept_encoder_args* a, void* base) {
   w.compact = p + off; off += align256(w.compact_bytes);
   w.attend_bytes = attend_workspace_bytes(a->n_tok, a->n_seq, a->n_heads, a->head_dim, a->seq_len);
   w.attend = p + off; off += align256(w.attend_bytes);
-  if (a->n_tok <= 64) {
-    w.skinny_bytes = std::max({skinny_ws_bytes(3 * dq, a->d_model), skinny_ws_bytes(a->d_model, dq),
-                               skinny_ws_bytes(a->d_ff, a->d_model),
-                               skinny_ws_bytes(a->d_model, a->d_ff)});
+  if (step_direct(a)) {
+    w.ticket = (unsigned long long*)(p + off);
+    off += 256;
+  } else if (a->n_tok <= 64) {
+    w.parts_bytes = std::max({skinny_ws_bytes(3 * dq, a->d_model), skinny_ws_bytes(a->d_model, dq),
+                              skinny_ws_bytes(a->d_ff, a->d_model),
+                              skinny_ws_bytes(a->d_model, a->d_ff)});
   } else {
-    w.skinny_bytes = std::max({mid_ws_bytes(a->n_tok, 3 * dq, a->d_model, EPI_QKV),
+    w.parts_bytes = std::max({mid_ws_bytes(a->n_tok, 3 * dq, a->d_model, EPI_QKV),
                                mid_ws_bytes(a->n_tok, a->d_model, dq, EPI_RESID),
                                mid_ws_bytes(a->n_tok, a->d_ff, a->d_model, EPI_GELU),
                                mid_ws_bytes(a->n_tok, a->d_model, a->d_ff, EPI_RESID)});
   }
-  if (w.skinny_bytes) {
-    w.skinny = (float*)(p + off);
-    off += align256(w.skinny_bytes);
+  if (w.parts_bytes) {
+    w.parts = (float*)(p + off);
+    off += align256(w.parts_bytes);
   }
   w.total = off;
   return w;
@@ -309,7 +320,13 @@ extern "C" adept_status adept_encoder_layer_step(const adept_encoder_args* a, in
   g.bias = off(a->b_qkv, (int64_t)li * 3 * dq);
   g.rows = act; g.head_dim = hd; g.d_q = dq;
   g.q_out = a->q_buf; g.k_cache = a->k_buf; g.v_cache = a->v_buf; g.name = "enc_gemm_qkv";
-  g.skinny_ws = ws.skinny; g.skinny_ws_bytes = ws.skinny_bytes;
+  g.skinny_ws = ws.parts; g.skinny_ws_bytes = ws.parts_bytes;
+  // few rows: LN2, the exit test, the early stop, the list update and the dead
+  // keys are one kernel, whose two words the first GEMM clears
+  const bool tail = step_direct(a) && exit_compact_fits(a->exit, D, maxn);
+  RowList list{};
+  list.ticket = ws.ticket;
+  if (tail) g.list = &list;
   ADEPT_TRY(gemm(ADEPT_BF16, g, s));
   // 2. bidirectional attention over the live rows of each sequence
   ADEPT_TRY(attend_dispatch(ADEPT_BF16, H, hd, 1.0f / sqrtf((float)hd), 0, a->q_buf, act, nact,
@@ -322,7 +339,7 @@ extern "C" adept_status adept_encoder_layer_step(const adept_encoder_args* a, in
   go.A = a->attn_out; go.lda = dq; go.B = off(a->w_o, (int64_t)li * D * dq); go.ldb = dq;
   go.epi = EPI_RESID; go.bias = off(a->b_o, (int64_t)li * D);
   go.C = a->y_buf; go.ldc = D; go.resid = a->h[in]; go.rows = act; go.name = "enc_gemm_o";
-  go.skinny_ws = ws.skinny; go.skinny_ws_bytes = ws.skinny_bytes;
+  go.skinny_ws = ws.parts; go.skinny_ws_bytes = ws.parts_bytes;
   ADEPT_TRY(gemm(ADEPT_BF16, go, s));
   ADEPT_TRY(layernorm_rows(D, a->ln_eps, a->y_buf, act, nact, maxn, off(a->ln1_g, (int64_t)li * D),
                            off(a->ln1_b, (int64_t)li * D), a->y_buf, s));
@@ -332,7 +349,7 @@ extern "C" adept_status adept_encoder_layer_step(const adept_encoder_args* a, in
   gi.A = a->y_buf; gi.a_rows = act; gi.lda = D; gi.B = off(a->w_in, (int64_t)li * F * D);
   gi.ldb = D; gi.epi = EPI_GELU; gi.bias = off(a->b_in, (int64_t)li * F);
   gi.C = a->ffn_act; gi.ldc = F; gi.name = "enc_gemm_in";
-  gi.skinny_ws = ws.skinny; gi.skinny_ws_bytes = ws.skinny_bytes;
+  gi.skinny_ws = ws.parts; gi.skinny_ws_bytes = ws.parts_bytes;
   ADEPT_TRY(gemm(ADEPT_BF16, gi, s));
   // 5. h_out = LN2(h1 + a W_out^T + b_out)
   GemmArgs gu{};
@@ -340,8 +357,20 @@ extern "C" adept_status adept_encoder_layer_step(const adept_encoder_args* a, in
   gu.A = a->ffn_act; gu.lda = F; gu.B = off(a->w_out, (int64_t)li * D * F); gu.ldb = F;
   gu.epi = EPI_RESID; gu.bias = off(a->b_out, (int64_t)li * D);
   gu.C = a->h[out]; gu.ldc = D; gu.resid = a->y_buf; gu.rows = act; gu.name = "enc_gemm_out";
-  gu.skinny_ws = ws.skinny; gu.skinny_ws_bytes = ws.skinny_bytes;
+  gu.skinny_ws = ws.parts; gu.skinny_ws_bytes = ws.parts_bytes;
   ADEPT_TRY(gemm(ADEPT_BF16, gu, s));
+  if (tail) {
+    ExitCompact x{};
+    x.d = D; x.layer = layer; x.max_active = maxn; x.cfg = &a->exit;
+    x.rows = act; x.n_active = nact; x.h = a->h[out]; x.inertia = a->inertia;
+    x.force_layer = a->force_layer; x.exit_flag = a->exit_flag; x.sim_out = a->sim_out;
+    x.next = a->active[out]; x.n_next = a->n_active[out];
+    x.exited = a->exited; x.n_exited = a->n_exited; x.exit_layer = a->exit_layer;
+    x.ticket = ws.ticket;
+    x.ln_g = off(a->ln2_g, (int64_t)li * D); x.ln_b = off(a->ln2_b, (int64_t)li * D);
+    x.ln_eps = a->ln_eps; x.cls_seq_len = a->cls_stop ? a->seq_len : 0; x.key_live = a->key_live;
+    return exit_compact(x, s);
+  }
   ADEPT_TRY(layernorm_rows(D, a->ln_eps, a->h[out], act, nact, maxn,
                            off(a->ln2_g, (int64_t)li * D), off(a->ln2_b, (int64_t)li * D),
                            a->h[out], s));

@@ -2,7 +2,8 @@
 // (B in nn.Linear [out][in] order, so both operands are K-contiguous).
 //
 // bf16 path: gemm_tile.h's 256x256 tile when the rows are many; 128x128 tiles
-// in gemm_mid.hip otherwise; the skinny path below for at most 64 rows.
+// in gemm_mid.hip otherwise; the skinny path below for 17 to 64 rows of wide
+// layers, gemm_direct.hip for the rest of them.
 //
 // Workgroups are mapped to tiles XCD by XCD: the hardware deals consecutive
 // workgroup ids round-robin to the 8 XCDs, so the id is remapped to give each
@@ -101,9 +102,9 @@ adept_status launch_bf16(const GP& p, hipStream_t s, const char* name) {
 }
 
 // ---------------------------------------------------------------------------
-// Skinny path (at most 64 rows: decode).  The weights are streamed from HBM
-// once; M is too small for the 256x256 tile to give the chip enough
-// workgroups.  The work is a flattened space of units: a unit is one
+// Skinny path (17 to 64 rows of wide layers: decode; fewer rows and narrower
+// layers: gemm_direct.hip).  The weights are streamed from HBM once; M is too
+// small for the 256x256 tile to give the chip enough workgroups.  The work is a flattened space of units: a unit is one
 // 64-column tile of the partial space (N columns, or the
 // F gate columns followed by the F up columns for SWIGLU) times one 64-deep
 // k step.  The units are cut into G equal contiguous ranges, one per
@@ -447,13 +448,18 @@ size_t skinny_ws_bytes(int Nt, int K) {
 }
 
 bool gemm_skinny_row_norm(const GemmArgs& g) {
-  return g.epi == EPI_RESID && g.M_max > 0 && g.M_max <= kSkinnyM && g.skinny_ws && g.N > 0 &&
-         g.N % 64 == 0 && g.N <= 4096 && g.K > 0 && g.K % BK == 0 &&
+  return g.epi == EPI_RESID && !gemm_direct_fits(g) && g.M_max > 0 && g.M_max <= kSkinnyM &&
+         g.skinny_ws && g.N > 0 && g.N % 64 == 0 && g.N <= 4096 && g.K > 0 && g.K % BK == 0 &&
          skinny_ws_bytes(g.N, g.K) <= g.skinny_ws_bytes;
 }
 
 adept_status gemm(adept_dtype dt, const GemmArgs& g, hipStream_t s) {
   if (g.M_max <= 0) return ADEPT_OK;
+  const bool direct = gemm_direct_fits(g);
+  if ((g.row_norm || g.list) && !direct) {
+    set_error("gemm: row_norm and list only where gemm_direct_fits");
+    return ADEPT_E_INVALID;
+  }
   if ((g.rinv_out || g.ln_out || g.exit) &&
       (!gemm_skinny_row_norm(g) || (!!g.rinv_out + !!g.ln_out + !!g.exit) > 1 ||
        (g.ln_out && !aligned8(g.ln_out)) ||
@@ -493,6 +499,7 @@ adept_status gemm(adept_dtype dt, const GemmArgs& g, hipStream_t s) {
     set_error("gemm: operands must be 16-byte aligned with leading dims a multiple of 8");
     return ADEPT_E_INVALID;
   }
+  if (direct) return gemm_direct(g, s);
   GP p = to_gp(g);
   if (g.M_max <= kSkinnyM && g.skinny_ws && g.epi != EPI_KV) {
     const int Nt = g.epi == EPI_SWIGLU ? 2 * g.N : g.N;

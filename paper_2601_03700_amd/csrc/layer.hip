@@ -33,10 +33,23 @@ struct LayerWs {
   void* prompt;   size_t prompt_bytes;   // per-sequence keys of the all-at-once variant
   void* hsm;      size_t hsm_bytes;      // mapper activations (when a mapper is given)
   float* skinny;  size_t skinny_bytes;   // GEMM partial sums (bf16)
+  unsigned long long* ticket;            // two words of exit_compact (step_direct)
   float* gemm_tmp;  // f32 path only
   void* xnorm;      // [n_tok][D] normalised rows (GPT2 family)
   size_t total;
 };
+
+// Whether all GEMMs of the step run as one kernel each (gemm_direct.hip), form
+// the RMSNorm factor of their rows (and the fused schedule's row list)
+// themselves, and leave the exit test to exit_compact.
+bool step_direct(const adept_layer_args* a) {
+  const int dq = a->n_heads * a->head_dim, D = a->d_model, F = a->d_ff, n = a->n_tok;
+  const bool gpt2 = a->family == ADEPT_FAMILY_GPT2;
+  return a->dtype == ADEPT_BF16 && gemm_direct_fits(n, 3 * dq, D, EPI_QKV) &&
+         gemm_direct_fits(n, D, dq, EPI_RESID) &&
+         gemm_direct_fits(n, gpt2 ? F : 2 * F, D, gpt2 ? EPI_GELU_TANH : EPI_SWIGLU) &&
+         gemm_direct_fits(n, D, F, EPI_RESID);
+}
 
 LayerWs carve(const adept_layer_args* a, void* base) {
   LayerWs w{};
@@ -63,7 +76,10 @@ LayerWs carve(const adept_layer_args* a, void* base) {
   w.prompt = p + off; off += align256(w.prompt_bytes);
   w.hsm_bytes = a->hsm ? adept_hsm_workspace_bytes(a->d_model, a->n_tok) : 0;
   w.hsm = p + off; off += align256(w.hsm_bytes);
-  if (a->dtype == ADEPT_BF16 && a->n_tok <= 64) {
+  if (step_direct(a)) {
+    w.ticket = (unsigned long long*)(p + off);
+    off += 256;
+  } else if (a->dtype == ADEPT_BF16 && a->n_tok <= 64) {
     w.skinny_bytes = std::max({skinny_ws_bytes(3 * dq, a->d_model), skinny_ws_bytes(a->d_model, dq),
                                skinny_ws_bytes(2 * a->d_ff, a->d_model),
                                skinny_ws_bytes(a->d_model, a->d_ff)});
@@ -309,10 +325,13 @@ extern "C" adept_status adept_layer_step(const adept_layer_args* a, int layer, v
   const int32_t* qrows = act;         // rows of the QKV GEMM
   const int32_t* nq = nact;
   const int qmax = fused ? a->n_tok : maxn;
+  const bool direct = step_direct(a);
+  const bool tail = direct && exit_compact_fits(a->exit, D, maxn) && a->exit.prompt_level == 0;
   // fused schedule: the row list and the QKV rows' norm (the RMSNorm
   // factors, or the LayerNorm rows when they fit one wave's registers) come
-  // from one kernel
-  const bool rinv_fused = fused && !gpt2 && dt == ADEPT_BF16 && qmax > 0;
+  // from one kernel, or from the GEMM itself (RMSNorm family, direct)
+  const bool list_fused = fused && !gpt2 && direct && qmax > 0;
+  const bool rinv_fused = fused && !gpt2 && dt == ADEPT_BF16 && !direct && qmax > 0;
   const int ln_r = ceil_div(ceil_div(D, 8), 64);   // 16-byte chunks per lane
   const bool ln_fused = fused && gpt2 && dt == ADEPT_BF16 && qmax > 0 && D % 8 == 0 &&
                         ln_r <= 8 && aligned16(a->h[0]) && aligned16(a->h[1]) &&
@@ -333,6 +352,8 @@ extern "C" adept_status adept_layer_step(const adept_layer_args* a, int layer, v
     exit_done = true;
     return ADEPT_OK;
   };
+  RowList list{};
+  list.ticket = tail ? ws.ticket : nullptr;
   if (rinv_fused) {
     ADEPT_LAUNCH(fused_rows_rinv_kernel<bf16>, fgrid, dim3(256), 0, s, a->n_tok, layer, D,
                  a->rms_eps, a->exit_layer, act, nact, maxn, (const bf16*)a->h[in],
@@ -355,12 +376,12 @@ extern "C" adept_status adept_layer_step(const adept_layer_args* a, int layer, v
       ADEPT_LAUNCH(fused_rows_ln_kernel<8>, fgrid, dim3(256), 0, s, a->n_tok, layer, D,
                    a->rms_eps, a->exit_layer, act, nact, maxn, xi, xo, lst, cnt, ws.fsel, xn);
     ADEPT_CHECK_LAUNCH("fused_rows_ln");
-  } else if (fused) {
+  } else if (fused && !list_fused) {
     ADEPT_LAUNCH(fused_rows_kernel, dim3(1), dim3(256), 0, s, a->n_tok, layer, a->exit_layer, act,
                  nact, maxn, ws.all_rows, ws.all_rows + a->n_tok, ws.fsel);
     ADEPT_CHECK_LAUNCH("fused_rows");
   }
-  if (fused) {
+  if (fused && !list_fused) {
     qrows = ws.all_rows;
     nq = ws.all_rows + a->n_tok;
   }
@@ -380,6 +401,7 @@ extern "C" adept_status adept_layer_step(const adept_layer_args* a, int layer, v
     g.rows = qrows; g.pos = a->pos; g.slot = a->slot; g.head_dim = hd; g.d_q = dq;
     g.q_out = a->q_buf; g.k_cache = kc; g.v_cache = vc; g.name = "gemm_qkv";
     g.skinny_ws = ws.skinny; g.skinny_ws_bytes = ws.skinny_bytes;
+    if (tail) g.list = &list;
     ADEPT_TRY(gemm(dt, g, s));
     // 3. attention over the mixed cache
     ADEPT_TRY(attend_dispatch(dt, H, hd, 1.0f / sqrtf((float)hd), 1, a->q_buf, act, nact, maxn,
@@ -419,10 +441,10 @@ extern "C" adept_status adept_layer_step(const adept_layer_args* a, int layer, v
     ADEPT_TRY(exit_in_epilogue(gd));
     ADEPT_TRY(gemm(dt, gd, s));
   } else if (qmax > 0) {
-    // the f32 GEMM forms the row factors itself
+    // the f32 GEMM and the direct one form the row factors themselves
     auto norm_in_gemm = [&](GemmArgs& x) {
       x.row_eps = a->rms_eps;
-      return dt == ADEPT_F32 && gemm_f32_fused(x);
+      return dt == ADEPT_F32 ? gemm_f32_fused(x) : direct;
     };
     // 1. pre-attention RMSNorm: the gain is folded into W_qkv, the row factor
     //    1/rms(h) scales the GEMM accumulators
@@ -430,7 +452,14 @@ extern "C" adept_status adept_layer_step(const adept_layer_args* a, int layer, v
     GemmArgs g{};
     g.M_max = qmax; g.M_dev = nq; g.N = 3 * dq; g.K = D;
     g.A = a->h[in]; g.a_rows = qrows; g.lda = D; g.B = wqkv; g.ldb = D; g.epi = EPI_QKV;
-    if (fused) { g.A2 = a->h[out]; g.a_sel = ws.fsel; }
+    if (list_fused) {
+      list.n_tok = a->n_tok; list.layer = layer; list.max_act = maxn;
+      list.exit_layer = a->exit_layer; list.act = act;
+      g.A2 = a->h[out];
+    } else if (fused) {
+      g.A2 = a->h[out]; g.a_sel = ws.fsel;
+    }
+    if (list_fused || tail) g.list = &list;
     g.row_scale = ws.rinv;
     g.rows = qrows; g.pos = a->pos; g.slot = a->slot;
     g.rope_cos = a->rope_cos; g.rope_sin = a->rope_sin; g.head_dim = hd; g.d_q = dq;
@@ -480,18 +509,30 @@ extern "C" adept_status adept_layer_step(const adept_layer_args* a, int layer, v
     ADEPT_TRY(exit_in_epilogue(gd));
     ADEPT_TRY(run_gemm(dt, gd, ws.gemm_tmp, s));
   }
-  // 8. exit test (Eq. 7-8), unless the down projection's epilogue ran it
-  if (!exit_done)
-    ADEPT_TRY(adept_exit_test(dt, D, layer, &a->exit, act, nact, maxn, a->h[out], a->h[in],
-                              a->inertia, a->force_layer, a->exit_flag, a->sim_out, stream));
-  // all-at-once variant (Appendix H.2): a prompt's last token decides for all of it
-  if (a->exit.prompt_level && a->attn_tiles)
-    ADEPT_TRY(adept_exit_prompt_level(act, nact, maxn, a->seq, a->pos, a->n_seq, a->exit_flag,
-                                      ws.prompt, ws.prompt_bytes, stream));
-  // 9. active-list update
-  ADEPT_TRY(adept_compact(layer, N, a->exit_flag, act, nact, maxn, a->active[out], a->n_active[out],
-                          a->exited, a->n_exited, a->exit_layer, ws.compact, ws.compact_bytes,
-                          stream));
+  if (tail) {
+    // 8. + 9. exit test and active-list update
+    ExitCompact x{};
+    x.d = D; x.layer = layer; x.max_active = maxn; x.cfg = &a->exit;
+    x.rows = act; x.n_active = nact; x.h = a->h[out]; x.inertia = a->inertia;
+    x.force_layer = a->force_layer; x.exit_flag = a->exit_flag; x.sim_out = a->sim_out;
+    x.next = a->active[out]; x.n_next = a->n_active[out];
+    x.exited = a->exited; x.n_exited = a->n_exited; x.exit_layer = a->exit_layer;
+    x.ticket = ws.ticket;
+    ADEPT_TRY(exit_compact(x, s));
+  } else {
+    // 8. exit test (Eq. 7-8), unless the down projection's epilogue ran it
+    if (!exit_done)
+      ADEPT_TRY(adept_exit_test(dt, D, layer, &a->exit, act, nact, maxn, a->h[out], a->h[in],
+                                a->inertia, a->force_layer, a->exit_flag, a->sim_out, stream));
+    // all-at-once variant (Appendix H.2): a prompt's last token decides for all of it
+    if (a->exit.prompt_level && a->attn_tiles)
+      ADEPT_TRY(adept_exit_prompt_level(act, nact, maxn, a->seq, a->pos, a->n_seq, a->exit_flag,
+                                        ws.prompt, ws.prompt_bytes, stream));
+    // 9. active-list update
+    ADEPT_TRY(adept_compact(layer, N, a->exit_flag, act, nact, maxn, a->active[out],
+                            a->n_active[out], a->exited, a->n_exited, a->exit_layer, ws.compact,
+                            ws.compact_bytes, stream));
+  }
   // 9b. mapper (Section 4.2) of the rows that exited here: s~ replaces h_i
   //     in place, so the K/V generation and the final state use it
   if (a->hsm && layer < N && maxn > 0)

@@ -1,0 +1,99 @@
+"""At most 64 rows: the GEMMs that run as one kernel (blocks of 16 rows, K in
+pieces of 64 over eight waves) and the exit test that updates the list itself,
+at the edges of the row blocks, with K shorter than the waves and a piece past
+the last whole round.  Whole layers with exits, each checked on the GPU's own
+inputs against the oracle (tests/layer_check.py: per element within max(2e-2,
+one bf16 ulp)); lists, flags and exit layers exact."""
+import math
+import sys
+
+import numpy as np
+import pytest
+
+import adept_inputs as ai
+from oracle import adept_oracle as O
+from paper_2601_03700_amd import binding as B
+from paper_2601_03700_amd.model import DecoderModel, EncoderModel
+from tests import layer_check as LC
+
+pytestmark = pytest.mark.gpu
+
+# K of 4, 9, 13 and 26 pieces; heads of 64 and 128
+LLAMA = ai.DecoderShape(n_layers=3, d_model=832, n_heads=6, head_dim=128, d_ff=1664, vocab=384)
+SMALL = ai.DecoderShape(n_layers=3, d_model=256, n_heads=4, head_dim=64, d_ff=640, vocab=320)
+# past the narrow-layer rule of 17 and more rows (down projection), wide blocks
+WIDE = ai.DecoderShape(n_layers=3, d_model=2048, n_heads=16, head_dim=128, d_ff=6272, vocab=256)
+GPT2 = ai.DecoderShape(n_layers=3, d_model=576, n_heads=9, head_dim=64, d_ff=1664, vocab=448,
+                       family="gpt2", max_pos=512)
+ENC = ai.EncoderShape(n_layers=3, d_model=768, n_heads=12, head_dim=64, d_ff=1600, vocab=500,
+                      max_pos=512)
+
+
+def say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+def _run(shape, seqs, rows, kv_fused=True, decode=False):
+    make = ai.gpt2_weights if shape.family == "gpt2" else ai.decoder_weights
+    w32 = make(shape, seed=rows, dtype="bf16")
+    model = DecoderModel(shape, w32, dtype="bf16", rope_max_pos=512)
+    model.kv_fused = kv_fused
+    cfg = B.exit_cfg(math.inf, shape.n_layers)
+    rng = np.random.default_rng(rows + seqs)
+    ids = ai.token_ids(rows, shape.vocab, seqs, rows)
+    force = rng.integers(0, shape.n_layers, size=ids.shape).astype(np.int32)
+    rep = LC.Report(say)
+    cache = model.new_cache(seqs, rows + 1)
+
+    def check(f):
+        return LC.DecoderLayerCheck(O.as64(w32), shape, cache, O.ExitConfig(delta=math.inf), "bf16",
+                                    force_layer=f, report=rep)
+    chk = check(force)
+    res, _ = model.prefill(ids, cfg, s_max=rows + 1, force_layer=force, logits="all", cache=cache,
+                           on_layer=chk)
+    chk.finish(res.state, res.logits, res.rows)
+    if decode:
+        import torch
+        f = rng.integers(0, shape.n_layers, size=seqs).astype(np.int32)
+        chk = check(f)
+        pos = torch.full((seqs,), rows, dtype=torch.int32, device="cuda")
+        nxt = torch.from_numpy(ai.token_ids(seqs, shape.vocab, 1, seqs).reshape(-1).astype(np.int32)).cuda()
+        r = model.decode_step(cache, nxt, pos, cfg, force_layer=torch.from_numpy(f).cuda(),
+                              on_layer=chk, pos_max=rows)
+        chk.finish(r.state, r.logits, r.rows)
+    rep.summary()
+
+
+@pytest.mark.parametrize("shape,rows", [(LLAMA, 1), (LLAMA, 16), (LLAMA, 17), (LLAMA, 33),
+                                        (LLAMA, 64), (SMALL, 5), (SMALL, 48), (WIDE, 16),
+                                        (WIDE, 17), (GPT2, 1), (GPT2, 16), (GPT2, 31), (GPT2, 64)])
+def test_prefill_rows(shape, rows):
+    say(f"few rows, prefill {shape.family} width={shape.d_model} rows={rows}")
+    _run(shape, 1, rows)
+
+
+@pytest.mark.parametrize("shape,seqs,kv_fused", [(LLAMA, 3, True), (LLAMA, 17, True), (SMALL, 64, True),
+                                                 (WIDE, 16, True), (SMALL, 33, False),
+                                                 (GPT2, 18, True), (GPT2, 64, False)])
+def test_decode_rows(shape, seqs, kv_fused):
+    say(f"few rows, decode {shape.family} width={shape.d_model} seqs={seqs} fused={kv_fused}")
+    _run(shape, seqs, 3, kv_fused, decode=True)
+
+
+@pytest.mark.parametrize("seqs,length", [(1, 1), (1, 17), (4, 16), (3, 11), (16, 4)])
+@pytest.mark.parametrize("stop", [True, False])
+def test_encoder_rows(seqs, length, stop):
+    say(f"few rows, encoder {seqs}x{length} stop={stop}")
+    rows = seqs * length
+    w32 = ai.encoder_weights(ENC, seed=rows, dtype="bf16")
+    ids = ai.token_ids(rows, ENC.vocab, seqs, length)
+    # also [CLS] rows leave early: their sequences stop
+    force = np.random.default_rng(rows).integers(0, ENC.n_layers, size=ids.shape).astype(np.int32)
+    rep = LC.Report(say)
+    chk = LC.EncoderLayerCheck(O.as64(w32), ENC, O.ExitConfig(delta=math.inf), force_layer=force,
+                               report=rep, stop_at_cls=stop)
+    out = EncoderModel(ENC, w32).classify(ids, B.exit_cfg(math.inf, ENC.n_layers),
+                                          force_layer=force, on_layer=chk, stop_at_cls=stop)
+    chk.finish(out, length)
+    rep.summary()
