@@ -44,8 +44,7 @@ TRAFFIC_FILES = (os.path.join(HERE, "profiles", "llama7b_generation_64x4096_hbm_
 # once any of them changes)
 FAMILY_SOURCES = {
     "gemm": ("gemm.hip", "gemm_tile.h", "gemm_mid.h", "gemm_mid.hip", "gemm_mid_128x128.hip",
-             "gemm_direct.hip",
-             "common.h"),
+             "gemm_direct.hip", "common.h"),
     "kv_generate": ("gemm.hip", "gemm_tile.h", "kvgen.hip", "common.h"),
     "attention": ("attention.hip", "common.h"), "attention_decode": ("attention.hip", "common.h"),
     "exit_test": ("exit_test.hip", "common.h"),

@@ -58,21 +58,44 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_bf16_kernel(GP p) {
 // that took items from per-XCD counters kept the loop's state in registers
 // and spilled 196 bytes per lane around the K loop; one item per workgroup
 // compiles as the plain GEMM does, without scratch, and runs 2 % faster.)
-template <int HD, bool EXT>
-__global__ __launch_bounds__(kThreads, 1) void gemm_kv_flat_kernel(GP p) {
+template <int HD, bool EXT, class GT>
+__global__ __launch_bounds__(GT::kThreads, GT::kTN == 128 ? 2 : 1) void gemm_kv_flat_kernel(GP p) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int n_work = *p.n_work;
+  constexpr int kSub = BM / GT::kTM;   // row tiles of an item: 256 rows
+  const int n_work = *p.n_work * kSub;
   const int total = n_work * p.tiles_n;
   const int chunk = (total + 7) >> 3;
   const int t = (int)(blockIdx.x & 7) * chunk + (int)(blockIdx.x >> 3);
   if ((int)(blockIdx.x >> 3) >= chunk || t >= total) return;
   int w, nt;
   raster_tile(t, n_work, p.tiles_n, &w, &nt);
-  const int packed = p.work[w];
-  const int layer = packed >> 16, mt = packed & 0xffff;
-  gemm_tile<EPI_KV, true, HD, EXT, GeoL, false>(p, smem, layer, mt, nt, p.grp_m[layer],
-                                               p.B + (int64_t)(layer - 1) * p.b_layer_stride, 0,
-                                               p.K / BK, nullptr);
+  const int packed = p.work[w / kSub];
+  const int layer = packed >> 16, mt = (packed & 0xffff) * kSub + w % kSub;
+  const int m = p.grp_m[layer];
+  if (kSub > 1 && mt * GT::kTM >= m) return;   // the item's second half is empty
+  gemm_tile<EPI_KV, true, HD, EXT, GT, false>(p, smem, layer, mt, nt, m,
+                                              p.B + (int64_t)(layer - 1) * p.b_layer_stride, 0,
+                                              p.K / BK, nullptr);
+}
+
+template <int HD, bool EXT, class GT>
+adept_status launch_kv_x(GP p, int max_work, hipStream_t s) {
+  static bool attr_set = false;
+  ADEPT_TRY(lds_limit((const void*)gemm_kv_flat_kernel<HD, EXT, GT>, GT::kLds, &attr_set,
+                      "kv LDS limit"));
+  p.tiles_n = ceil_div(p.N, GT::kTN);
+  // one workgroup per tile: the host bound on them, rounded to whole XCD rounds
+  const int flat = (max_work * (BM / GT::kTM) * p.tiles_n + 7) / 8 * 8;
+  ADEPT_LAUNCH((gemm_kv_flat_kernel<HD, EXT, GT>), dim3(flat), dim3(GT::kThreads), GT::kLds, s, p);
+  return launch_status("gemm_kv_grouped");
+}
+
+template <class GT>
+adept_status launch_kv(const GP& p, int max_work, hipStream_t s) {
+  const bool ext = tile_needs_ext(p, EPI_KV, GT::kTN) || p.bias;
+  if (p.head_dim == 128)
+    return ext ? launch_kv_x<128, true, GT>(p, max_work, s) : launch_kv_x<128, false, GT>(p, max_work, s);
+  return ext ? launch_kv_x<64, true, GT>(p, max_work, s) : launch_kv_x<64, false, GT>(p, max_work, s);
 }
 
 // Sets a kernel's dynamic-LDS limit once per process.
@@ -558,28 +581,14 @@ adept_status gemm_kv_grouped(const GemmArgs& g, const int32_t* work, const int32
   p.work = work; p.n_work = n_work; p.grp_m = grp_m; p.srows = srows;
   p.b_layer_stride = b_layer_stride;
   p.cache_layer_stride = cache_layer_stride;
-  p.tiles_n = ceil_div(g.N, BN);
-  const bool ext = needs_ext(p, EPI_KV) || (g.bias != nullptr);
-  // one workgroup per item: the host bound on the items, rounded to whole XCD rounds
-  const int flat = (max_work * p.tiles_n + 7) / 8 * 8;
-  if (g.head_dim == 128 && !ext) {
-    static bool attr_set = false;
-    ADEPT_TRY(allow_lds((const void*)gemm_kv_flat_kernel<128, false>, &attr_set, "kv LDS limit"));
-    ADEPT_LAUNCH((gemm_kv_flat_kernel<128, false>), dim3(flat), dim3(kThreads), kLdsBytes, s, p);
-  } else if (g.head_dim == 128) {
-    static bool attr_set = false;
-    ADEPT_TRY(allow_lds((const void*)gemm_kv_flat_kernel<128, true>, &attr_set, "kv LDS limit"));
-    ADEPT_LAUNCH((gemm_kv_flat_kernel<128, true>), dim3(flat), dim3(kThreads), kLdsBytes, s, p);
-  } else if (!ext) {
-    static bool attr_set = false;
-    ADEPT_TRY(allow_lds((const void*)gemm_kv_flat_kernel<64, false>, &attr_set, "kv LDS limit"));
-    ADEPT_LAUNCH((gemm_kv_flat_kernel<64, false>), dim3(flat), dim3(kThreads), kLdsBytes, s, p);
-  } else {
-    static bool attr_set = false;
-    ADEPT_TRY(allow_lds((const void*)gemm_kv_flat_kernel<64, true>, &attr_set, "kv LDS limit"));
-    ADEPT_LAUNCH((gemm_kv_flat_kernel<64, true>), dim3(flat), dim3(kThreads), kLdsBytes, s, p);
-  }
-  return launch_status("gemm_kv_grouped");
+  // Few tiles (one or two skipped layers): a tile's latency is the time, so
+  // 128x128 tiles, two per CU.  Two layers, 20 to 30 % of the rows leaving after
+  // the first: 7B width, 333 rows 636 -> 608 us, 1500 rows 1311 -> 1291; width
+  // 1600, 750 rows 351 -> 315, 7200 rows (377 tiles) 1263 -> 1244.  With more
+  // tiles the smaller ones' loads through L2 bind: 600 rows over 24 layers of
+  // the 7B width 841 -> 909 us, 4096 rows 2970 -> 3970.
+  if ((int64_t)max_work * ceil_div(g.N, BN) <= 512) return launch_kv<Geo<128, 128>>(p, max_work, s);
+  return launch_kv<GeoL>(p, max_work, s);
 }
 
 }  // namespace adept

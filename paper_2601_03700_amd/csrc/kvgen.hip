@@ -171,17 +171,17 @@ extern "C" size_t adept_kv_generate_workspace_bytes(int n_layers, int max_rows) 
   return total;
 }
 
-extern "C" adept_status adept_kv_generate(adept_dtype dt, int n_layers, int d_model, int n_heads,
-                                          int head_dim, float eps, const void* s_map,
-                                          const int32_t* rows, const int32_t* n_rows,
-                                          int max_rows, const int32_t* exit_layer,
-                                          const int32_t* cache_slot, const int32_t* pos,
-                                          const void* w_kv, int64_t w_kv_layer_stride,
-                                          const void* attn_gain, const float* rope_cos,
-                                          const float* rope_sin, int rope_max_pos,
-                                          void* k_cache, void* v_cache, int64_t n_slots,
-                                          void* workspace, size_t workspace_bytes,
-                                          void* stream) {
+adept_status adept::kv_generate_upto(int max_skipped, adept_dtype dt, int n_layers, int d_model, int n_heads,
+                                     int head_dim, float eps, const void* s_map,
+                                     const int32_t* rows, const int32_t* n_rows,
+                                     int max_rows, const int32_t* exit_layer,
+                                     const int32_t* cache_slot, const int32_t* pos,
+                                     const void* w_kv, int64_t w_kv_layer_stride,
+                                     const void* attn_gain, const float* rope_cos,
+                                     const float* rope_sin, int rope_max_pos,
+                                     void* k_cache, void* v_cache, int64_t n_slots,
+                                     void* workspace, size_t workspace_bytes,
+                                     void* stream) {
   ADEPT_REQUIRE(dt == ADEPT_F32 || dt == ADEPT_BF16, "kv_generate: bad dtype");
   ADEPT_REQUIRE(n_layers >= 1 && n_layers <= kMaxLayers, "kv_generate: n_layers %d", n_layers);
   ADEPT_REQUIRE(d_model > 0 && n_heads > 0 && head_dim > 0 && head_dim % 2 == 0,
@@ -245,9 +245,26 @@ extern "C" adept_status adept_kv_generate(adept_dtype dt, int n_layers, int d_mo
   g.epi = EPI_KV; g.pos = pos; g.slot = cache_slot;
   g.rope_cos = rope_cos; g.rope_sin = rope_sin; g.head_dim = head_dim; g.d_q = dq;
   g.k_cache = k_cache; g.v_cache = v_cache; g.row_scale = w.rinv;
-  const int max_work = n_layers * ceil_div(max_rows, kTileM);
+  const int max_work = max_skipped * ceil_div(max_rows, kTileM);
   return gemm_kv_grouped(g, w.work, w.n_work, max_work, w.grp_m, w.srows,
                          w_kv_layer_stride, layer_stride, s);
+}
+
+extern "C" adept_status adept_kv_generate(adept_dtype dt, int n_layers, int d_model, int n_heads,
+                                          int head_dim, float eps, const void* s_map,
+                                          const int32_t* rows, const int32_t* n_rows,
+                                          int max_rows, const int32_t* exit_layer,
+                                          const int32_t* cache_slot, const int32_t* pos,
+                                          const void* w_kv, int64_t w_kv_layer_stride,
+                                          const void* attn_gain, const float* rope_cos,
+                                          const float* rope_sin, int rope_max_pos,
+                                          void* k_cache, void* v_cache, int64_t n_slots,
+                                          void* workspace, size_t workspace_bytes,
+                                          void* stream) {
+  return kv_generate_upto(n_layers, dt, n_layers, d_model, n_heads, head_dim, eps, s_map, rows,
+                          n_rows, max_rows, exit_layer, cache_slot, pos, w_kv, w_kv_layer_stride,
+                          attn_gain, rope_cos, rope_sin, rope_max_pos, k_cache, v_cache, n_slots,
+                          workspace, workspace_bytes, stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -276,8 +293,8 @@ extern "C" size_t adept_kv_generate_layernorm_workspace_bytes(int n_layers, int 
   return ln_total(n_layers, max_rows, d_model, &off);
 }
 
-extern "C" adept_status adept_kv_generate_layernorm(
-    adept_dtype dt, int n_layers, int d_model, int n_heads, int head_dim, float eps,
+adept_status adept::kv_generate_layernorm_upto(
+    int max_skipped, adept_dtype dt, int n_layers, int d_model, int n_heads, int head_dim, float eps,
     const void* s_map, const int32_t* rows, const int32_t* n_rows, int max_rows,
     const int32_t* exit_layer, const int32_t* cache_slot, const void* w_kv,
     int64_t w_kv_layer_stride, const void* b_kv, int64_t b_kv_layer_stride, void* k_cache,
@@ -323,9 +340,21 @@ extern "C" adept_status adept_kv_generate_layernorm(
   g.epi = EPI_KV; g.slot = cache_slot; g.head_dim = head_dim; g.d_q = dq;
   g.k_cache = k_cache; g.v_cache = v_cache;
   g.bias = b_kv; g.bias_layer_stride = b_kv_layer_stride;
-  const int max_work = n_layers * ceil_div(max_rows, kTileM);
+  const int max_work = max_skipped * ceil_div(max_rows, kTileM);
   return gemm_kv_grouped(g, w.work, w.n_work, max_work, w.grp_m, w.srows,
                          w_kv_layer_stride, n_slots * dq, s);
+}
+
+extern "C" adept_status adept_kv_generate_layernorm(
+    adept_dtype dt, int n_layers, int d_model, int n_heads, int head_dim, float eps,
+    const void* s_map, const int32_t* rows, const int32_t* n_rows, int max_rows,
+    const int32_t* exit_layer, const int32_t* cache_slot, const void* w_kv,
+    int64_t w_kv_layer_stride, const void* b_kv, int64_t b_kv_layer_stride, void* k_cache,
+    void* v_cache, int64_t n_slots, void* workspace, size_t workspace_bytes, void* stream) {
+  return kv_generate_layernorm_upto(n_layers, dt, n_layers, d_model, n_heads, head_dim, eps, s_map,
+                                    rows, n_rows, max_rows, exit_layer, cache_slot, w_kv,
+                                    w_kv_layer_stride, b_kv, b_kv_layer_stride, k_cache, v_cache,
+                                    n_slots, workspace, workspace_bytes, stream);
 }
 
 // ---------------------------------------------------------------------------

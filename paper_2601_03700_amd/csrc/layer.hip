@@ -235,7 +235,8 @@ adept_status run_gemm(adept_dtype dt, const GemmArgs& g, float* tmp, hipStream_t
 
 // Eq. 9 for the rows listed in rows / n_rows: the K and V rows of each
 // layer's stacked QKV weight (and, for the GPT2 family, of its folded bias).
-adept_status kv_generate_family(const adept_layer_args* a, adept_dtype dt, const void* s_map,
+adept_status kv_generate_family(const adept_layer_args* a, int max_skipped, adept_dtype dt,
+                                const void* s_map,
                                 const int32_t* rows, const int32_t* n_rows, int max_rows,
                                 const LayerWs& ws, void* stream) {
   const int N = a->n_layers, D = a->d_model, H = a->n_heads, hd = a->head_dim;
@@ -243,12 +244,12 @@ adept_status kv_generate_family(const adept_layer_args* a, adept_dtype dt, const
   const size_t esz = dt == ADEPT_BF16 ? 2 : 4;
   const void* wkv = (const char*)a->w_qkv + dq * D * (int64_t)esz;
   if (a->family == ADEPT_FAMILY_GPT2)
-    return adept_kv_generate_layernorm(dt, N, D, H, hd, a->rms_eps, s_map, rows, n_rows, max_rows,
+    return kv_generate_layernorm_upto(max_skipped, dt, N, D, H, hd, a->rms_eps, s_map, rows, n_rows, max_rows,
                                        a->exit_layer, a->slot, wkv, 3 * dq * D,
                                        (const char*)a->b_qkv + dq * (int64_t)esz, 3 * dq,
                                        a->k_cache, a->v_cache, a->n_slots, ws.kvgen,
                                        ws.kvgen_bytes, stream);
-  return adept_kv_generate(dt, N, D, H, hd, a->rms_eps, s_map, rows, n_rows, max_rows,
+  return kv_generate_upto(max_skipped, dt, N, D, H, hd, a->rms_eps, s_map, rows, n_rows, max_rows,
                            a->exit_layer, a->slot, a->pos, wkv, 3 * dq * D, nullptr, a->rope_cos,
                            a->rope_sin, a->rope_max_pos, a->k_cache, a->v_cache, a->n_slots,
                            ws.kvgen, ws.kvgen_bytes, stream);
@@ -548,11 +549,11 @@ extern "C" adept_status adept_layer_step(const adept_layer_args* a, int layer, v
                  a->exit_layer, (const char*)a->h[(N + 1) & 1], (char*)a->h[N & 1], ws.all_rows,
                  ws.all_rows + a->n_tok);
     ADEPT_CHECK_LAUNCH("defer_rows");
-    ADEPT_TRY(kv_generate_family(a, dt, a->h[N & 1], ws.all_rows, ws.all_rows + a->n_tok,
+    ADEPT_TRY(kv_generate_family(a, N, dt, a->h[N & 1], ws.all_rows, ws.all_rows + a->n_tok,
                                  a->n_tok, ws, stream));
   }
   if (!defer && layer < N && maxn > 0) {
-    ADEPT_TRY(kv_generate_family(a, dt, a->h[out], a->exited, a->n_exited, maxn, ws, stream));
+    ADEPT_TRY(kv_generate_family(a, N - layer, dt, a->h[out], a->exited, a->n_exited, maxn, ws, stream));
   }
   return ADEPT_OK;
 }
