@@ -105,6 +105,13 @@ constexpr int QT = 128;  // queries per tile (4 waves x 2 groups of 16)
 constexpr int kPrefillThreads = 256;
 constexpr int KB = 64;   // keys per LDS block
 
+// Lists up to this many entries find the sequences' first entries by reading
+// the whole list once (each entry against its predecessor, the loads of a pass
+// independent); longer ones by binary search.  A search is a chain of two
+// loads per halving: 6.2 us for 3 sequences of 250, 3.7 with the scan; but one
+// workgroup's loads bind the scan of 26000 entries (31 us, the search 23).
+constexpr int kPlanScan = 4096;
+
 __global__ __launch_bounds__(1024) void attend_plan_kernel(const int32_t* __restrict__ rows,
                                                            const int32_t* __restrict__ n_active,
                                                            int max_active,
@@ -115,30 +122,66 @@ __global__ __launch_bounds__(1024) void attend_plan_kernel(const int32_t* __rest
   int* seg = psm;
   int* toff = psm + n_seq + 1;
   const int n = min(*n_active, max_active);
-  for (int b = threadIdx.x; b <= n_seq; b += blockDim.x) {
-    // first entry whose sequence is >= b (sequence ids are non-decreasing)
-    int lo = 0, hi = n;
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (seq[rows[mid]] < b) lo = mid + 1; else hi = mid;
+  if (n <= kPlanScan) {
+    // first entry whose sequence is >= b: the least entry with b in (before, at]
+    // (the ids are non-decreasing; the least keeps the starts in order whatever
+    // they are); no such entry: n
+    for (int b = threadIdx.x; b <= n_seq; b += 1024) seg[b] = n;
+    __syncthreads();
+    constexpr int kU = 4;        // entries of a thread in flight
+    for (int k0 = threadIdx.x; k0 <= n; k0 += 1024 * kU) {
+      int at[kU], before[kU];
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int k = k0 + 1024 * u;
+        at[u] = k < n ? rows[k] : -1;
+        before[u] = k > 0 && k <= n ? rows[k - 1] : -1;
+      }
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        at[u] = at[u] >= 0 ? seq[at[u]] : n_seq;
+        before[u] = before[u] >= 0 ? seq[before[u]] : -1;
+      }
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int k = k0 + 1024 * u;
+        if (k > n) break;
+        for (int b = max(before[u], -1) + 1; b <= min(at[u], n_seq); ++b) atomicMin(&seg[b], k);
+      }
     }
-    seg[b] = lo;
+  } else {
+    for (int b = threadIdx.x; b <= n_seq; b += blockDim.x) {
+      int lo = 0, hi = n;
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (seq[rows[mid]] < b) lo = mid + 1; else hi = mid;
+      }
+      seg[b] = lo;
+    }
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < 64) {   // exclusive scan of the sequences' tile counts
     int acc = 0;
-    for (int b = 0; b < n_seq; ++b) {
-      toff[b] = acc;
-      acc += (seg[b + 1] - seg[b] + QT - 1) / QT;
+    for (int b0 = 0; b0 < n_seq; b0 += 64) {
+      const int b = b0 + threadIdx.x;
+      const int c = b < n_seq ? (seg[b + 1] - seg[b] + QT - 1) / QT : 0;
+      int x = c;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(x, o, 64);
+        if ((int)threadIdx.x >= o) x += y;
+      }
+      if (b < n_seq) toff[b] = acc + x - c;
+      acc += __shfl(x, 63, 64);
     }
-    toff[n_seq] = acc;
-    *n_tiles = acc;
+    if (threadIdx.x == 0) *n_tiles = acc;
   }
   __syncthreads();
-  for (int b = 0; b < n_seq; ++b) {
+  // a wave per sequence
+  for (int b = threadIdx.x >> 6; b < n_seq; b += blockDim.x >> 6) {
     const int cnt = seg[b + 1] - seg[b];
     const int nt = (cnt + QT - 1) / QT;
-    for (int t = threadIdx.x; t < nt; t += blockDim.x)
+    for (int t = threadIdx.x & 63; t < nt; t += 64)
       tiles[toff[b] + t] = make_int2(seg[b] + t * QT, min(QT, cnt - t * QT));
   }
 }
