@@ -2,8 +2,8 @@
 // decoder's epilogues, on the f32 matrix instruction (f32 products and sums).
 //
 // Main form: one workgroup per 16 x 16 outputs (QKV and SwiGLU: per 16 x 2 x 16,
-// a block of columns and its rotary partner, or gate and up), its four waves
-// taking every fourth 32-deep piece of K; the waves' sums meet in LDS, in
+// a block of columns and its rotary partner, or gate and up), its four or
+// sixteen waves taking every fourth or sixteenth 32-deep piece of K; the waves' sums meet in LDS, in
 // wave order, where the epilogue runs, with the row's RMSNorm factor formed
 // from the A values on the way when asked.  The shapes are small (128 x 256,
 // K = 1024): what bounds them is the chip they leave idle and the chain of
@@ -20,8 +20,6 @@
 namespace adept {
 namespace {
 
-constexpr int kF32Waves = 4;
-
 // EPI_KV, the KV generation (blockIdx.z: layer - 1): K and V of the listed rows
 // that exited before the layer, with the layer's norm gain when it is not
 // folded into the weights.
@@ -30,12 +28,12 @@ struct KvF32 {
   const float* gain;      // [n_layers][K], nullable
 };
 
-template <int EPI, bool NORM>
-__global__ __launch_bounds__(64 * kF32Waves) void gemm_f32_mfma_kernel(GP p, KvF32 kv) {
+template <int EPI, bool NORM, int W>
+__global__ __launch_bounds__(64 * W) void gemm_f32_mfma_kernel(GP p, KvF32 kv) {
   constexpr bool kCache = EPI == EPI_QKV || EPI == EPI_KV;
   constexpr int NB = kCache || EPI == EPI_SWIGLU ? 2 : 1;
-  __shared__ float red[kF32Waves][NB][16][17];
-  __shared__ float ssq[kF32Waves][16];
+  __shared__ float red[W][NB][16][17];
+  __shared__ float ssq[W][16];
   const int M = p.M_dev ? min(*p.M_dev, p.M_max) : p.M_max;
   const int m0 = blockIdx.x * 16;
   if (m0 >= M) return;
@@ -91,7 +89,7 @@ __global__ __launch_bounds__(64 * kF32Waves) void gemm_f32_mfma_kernel(GP p, KvF
   // lane (row r16, q) holds k = k0 + 16 h + 4 q + 0..3 of both operands, so the
   // instruction's four k are 4 q + e of the four q, for e = 0..3.  Four of the
   // wave's 32-deep pieces are loaded at once.
-  constexpr int U = 2, kStep = 32 * kF32Waves;
+  constexpr int U = 2, kStep = 32 * W;
 #pragma unroll 1
   for (int kb = 32 * wave; kb < p.K; kb += U * kStep) {
     float4 a[U][2], b[NB][U][2];
@@ -143,18 +141,18 @@ __global__ __launch_bounds__(64 * kF32Waves) void gemm_f32_mfma_kernel(GP p, KvF
     if (q == 0) ssq[wave][r16] = ss;
   }
   __syncthreads();
-  if (m >= M || n >= p.N) return;
+  if (threadIdx.x >= 256 || m >= M || n >= p.N) return;
   float x[NB];
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
     x[b] = 0.0f;
 #pragma unroll
-    for (int w = 0; w < kF32Waves; ++w) x[b] += red[w][b][r][c];
+    for (int w = 0; w < W; ++w) x[b] += red[w][b][r][c];
   }
   if (NORM) {
     float t = 0.0f;
 #pragma unroll
-    for (int w = 0; w < kF32Waves; ++w) t += ssq[w][r];
+    for (int w = 0; w < W; ++w) t += ssq[w][r];
     sc = 1.0f / sqrtf(t / (float)p.K + p.row_eps);
   }
   float* C = reinterpret_cast<float*>(p.C);
@@ -184,12 +182,23 @@ __global__ __launch_bounds__(64 * kF32Waves) void gemm_f32_mfma_kernel(GP p, KvF
   }
 }
 
+// Sixteen waves for the two-block epilogues, whose rows are norms and weights of
+// K = 256 (QKV 10.0 -> 8.6 us, gate/up 14.2 -> 12.9, K/V generation 11.4 ->
+// 10.0 at 128 rows); four for the others (O and down projections 11.8, with
+// sixteen 12.4: the sums of more waves cost what the shorter chain gains).
+template <int EPI>
+adept_status launch_f32_grid(const GP& p, const KvF32& kv, const dim3& grid, bool norm,
+                             hipStream_t s) {
+  constexpr int W = EPI == EPI_QKV || EPI == EPI_KV || EPI == EPI_SWIGLU ? 16 : 4;
+  const dim3 block(64 * W);
+  if (norm) ADEPT_LAUNCH((gemm_f32_mfma_kernel<EPI, true, W>), grid, block, 0, s, p, kv);
+  else ADEPT_LAUNCH((gemm_f32_mfma_kernel<EPI, false, W>), grid, block, 0, s, p, kv);
+  return launch_status("gemm_f32");
+}
+
 template <int EPI> adept_status launch_f32_epi(const GP& p, bool norm, hipStream_t s) {
   const int cols = EPI == EPI_QKV ? p.N / 2 : p.N;
-  const dim3 grid(ceil_div(p.M_max, 16), ceil_div(cols, 16)), block(64 * kF32Waves);
-  if (norm) ADEPT_LAUNCH((gemm_f32_mfma_kernel<EPI, true>), grid, block, 0, s, p, KvF32{});
-  else ADEPT_LAUNCH((gemm_f32_mfma_kernel<EPI, false>), grid, block, 0, s, p, KvF32{});
-  return launch_status("gemm_f32");
+  return launch_f32_grid<EPI>(p, KvF32{}, dim3(ceil_div(p.M_max, 16), ceil_div(cols, 16)), norm, s);
 }
 
 adept_status launch_f32(const GemmArgs& g, hipStream_t s) {
@@ -316,10 +325,8 @@ adept_status kvgen_f32_fused(const GemmArgs& g, int n_layers, const int32_t* exi
   GP p = to_gp(g);
   p.b_layer_stride = b_layer_stride;
   p.cache_layer_stride = cache_layer_stride;
-  const dim3 grid(ceil_div(p.M_max, 16), p.N / 32, n_layers), block(64 * kF32Waves);
-  ADEPT_LAUNCH((gemm_f32_mfma_kernel<EPI_KV, true>), grid, block, 0, s, p,
-               KvF32{exit_layer, gain});
-  return launch_status("kvgen_f32");
+  return launch_f32_grid<EPI_KV>(p, KvF32{exit_layer, gain},
+                                 dim3(ceil_div(p.M_max, 16), p.N / 32, n_layers), true, s);
 }
 
 // f32 GEMM + element-wise epilogue; tmp holds M_max x (N or 2N for SWIGLU) floats.
