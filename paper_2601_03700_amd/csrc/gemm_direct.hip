@@ -352,7 +352,10 @@ template <int EPI>
 adept_status dir_rows(const GP& p, const RowList& rl, int row_norm, const char* name,
                       hipStream_t s) {
   const int M = rl.exit_layer ? rl.n_tok : p.M_max;
-  if (M <= 16) return dir_launch<EPI, 1, 1, 8, 2>(p, rl, row_norm, name, s);
+  // one piece of K in flight per stage for QKV, whose workgroups (768 of them at
+  // the 7B width) are short and start with the row list: more of them per CU
+  // (28 -> 24 us); two for the others (down and O projections 18 -> 15.6)
+  if (M <= 16) return dir_launch<EPI, 1, 1, 8, EPI == EPI_QKV ? 1 : 2>(p, rl, row_norm, name, s);
   // 32 weight rows per workgroup where they still give half the chip one: the
   // activations are read half as often (24 rows, width 1600: QKV 14.0 -> 11.0 us
   // with 150 workgroups, but the O and down projections 12.4 -> 18.1 with 50)
