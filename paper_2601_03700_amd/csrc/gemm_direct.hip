@@ -370,13 +370,17 @@ adept_status dir_rows(const GP& p, const RowList& rl, int row_norm, const char* 
 }  // namespace
 
 // Up to 16 rows, or up to 64 of narrow layers.  With more rows each workgroup
-// reads 64 activation rows for 16 or 32 weight rows, and the load path of the
-// CUs binds: at the 7B widths and 64 rows 35 to 73 us a GEMM, 16 to 43 for the
-// skinny path's two kernels; at width 1600 and 24 rows 10 to 12 against 13.
+// reads up to 64 activation rows for 16 or 32 weight rows, and the load path of
+// the CUs binds: at the 7B widths and 64 rows 35 to 73 us a GEMM, 16 to 43 for
+// the skinny path's two kernels; at width 1600 (10 M weights) a decode step of
+// 24 rows 4000 us against 4530, of 40 4471 against 4661, of 48 the same, of 64
+// 5412 against 5141 (5246 with only the O projection, 2.6 M, on it); at width
+// 768 (2.4 M) and 64 rows 713 against 789.
 // Plain stores (the head) of wide layers stream better through the tiles of
 // gemm_mid.h (6 rows, 32000 x 4096: 52 us, 58 here).
 bool gemm_direct_fits(int M_max, int n_weights, int K, int epi) {
-  const bool narrow = (int64_t)n_weights * K <= (12 << 20);
+  const int64_t weights = (int64_t)n_weights * K;
+  const bool narrow = weights <= (M_max <= 40 ? 12 << 20 : 2400000);
   return M_max > 0 && M_max <= kDirectRows && epi != EPI_KV &&
          (narrow || (M_max <= 16 && epi != EPI_STORE));
 }
