@@ -1,0 +1,52 @@
+"""Classification does not depend on which kernels the row count selects: the
+encoder's GEMMs keep one order of sums up to 64 rows and one above, so a
+sequence's states and logits are the same bits alone and in any batch of its
+side of that line.  (A change of order turns up as a few changed bf16 roundings
+per layer, and after twelve layers as several percent of two class logits.)"""
+import math
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import adept_inputs as ai
+from paper_2601_03700_amd import binding as B
+from paper_2601_03700_amd.model import EncoderModel
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+BASE = ai.EncoderShape(n_layers=3, d_model=768, n_heads=12, head_dim=64, d_ff=3072, vocab=500,
+                       max_pos=512)
+
+
+def _final(model, shape, ids, force):
+    """(logits, final state of every row, exit layers) of one call."""
+    r = model.classify(ids, B.exit_cfg(math.inf, shape.n_layers), force_layer=force)
+    el = r.exit_layer.clone()
+    odd = (el & 1).bool()[:, None]
+    return r.logits.clone(), torch.where(odd, r.state["h"][1], r.state["h"][0]), el
+
+
+def _same_alone_and_beside(shape, length, counts):
+    print(f"encoder width={shape.d_model} length={length} sequences={counts}", flush=True)
+    sys.stdout.flush()
+    model = EncoderModel(shape, ai.encoder_weights(shape, seed=length, dtype="bf16"))
+    n = max(counts)
+    ids = ai.token_ids(length, shape.vocab, n, length)
+    rng = np.random.default_rng(length)
+    force = (rng.random(ids.shape) < 0.3) * rng.integers(1, shape.n_layers, size=ids.shape)
+    force[::3, 0] = 0                     # some [CLS] rows leave early, some stay
+    force = force.astype(np.int32)
+    want = _final(model, shape, ids, force)
+    for b in counts:
+        lg, h, el = _final(model, shape, ids[:b], force[:b])
+        assert torch.equal(el, want[2][:b * length])
+        assert torch.equal(h, want[1][:b * length])
+        assert torch.equal(lg, want[0][:b])
+
+
+@pytest.mark.parametrize("length,counts", [(70, (1, 2, 58)), (129, (1, 5, 30)), (300, (1, 8, 20))])
+def test_more_than_64_rows(length, counts):
+    _same_alone_and_beside(BASE, length, counts)
