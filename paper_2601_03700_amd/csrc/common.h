@@ -87,15 +87,7 @@ __device__ __forceinline__ bool exit_decision(bool pass, int layer, int min_exit
 // access is a 16-byte vector.  Mean and variance in f32 from the registers
 // (two passes); o = (x - mean) / sqrt(var + eps) [* gain + bias].  o may be x.
 template <int R>
-__device__ __forceinline__ void layernorm_regs(float (&v)[R][8], float s, int d, float eps,
-                                               const bf16* __restrict__ gain,
-                                               const bf16* __restrict__ bias, bf16* o, int lane);
-template <int R>
-__device__ __forceinline__ void layernorm_row_vec(const bf16* x, int d, float eps,
-                                                  const bf16* __restrict__ gain,
-                                                  const bf16* __restrict__ bias, bf16* o,
-                                                  int lane) {
-  float v[R][8];
+__device__ __forceinline__ float layernorm_load(const bf16* x, int d, int lane, float (&v)[R][8]) {
   float s = 0.0f;
 #pragma unroll
   for (int j = 0; j < R; ++j) {
@@ -110,14 +102,14 @@ __device__ __forceinline__ void layernorm_row_vec(const bf16* x, int d, float ep
       s += v[j][2 * e] + v[j][2 * e + 1];
     }
   }
-  layernorm_regs<R>(v, s, d, eps, gain, bias, o, lane);
+  return s;   // the lane's sum
 }
 
-// The rest of it: the row in registers (zeros past d), s the lane's sum.
+// The row in registers (zeros past d), s the lane's sum: the mean and
+// 1/sqrt(var + eps).
 template <int R>
-__device__ __forceinline__ void layernorm_regs(float (&v)[R][8], float s, int d, float eps,
-                                               const bf16* __restrict__ gain,
-                                               const bf16* __restrict__ bias, bf16* o, int lane) {
+__device__ __forceinline__ float2 layernorm_stats(const float (&v)[R][8], float s, int d, float eps,
+                                                  int lane) {
   const float mean = wave_sum_f32(s) / (float)d;
   float q = 0.0f;
 #pragma unroll
@@ -129,7 +121,13 @@ __device__ __forceinline__ void layernorm_regs(float (&v)[R][8], float s, int d,
       q = fmaf(t, t, q);
     }
   }
-  const float r = 1.0f / sqrtf(wave_sum_f32(q) / (float)d + eps);
+  return make_float2(mean, 1.0f / sqrtf(wave_sum_f32(q) / (float)d + eps));
+}
+
+template <int R>
+__device__ __forceinline__ void layernorm_apply(const float (&v)[R][8], float mean, float r, int d,
+                                                const bf16* __restrict__ gain,
+                                                const bf16* __restrict__ bias, bf16* o, int lane) {
 #pragma unroll
   for (int j = 0; j < R; ++j) {
     const int c = (lane + 64 * j) * 8;
@@ -153,6 +151,17 @@ __device__ __forceinline__ void layernorm_regs(float (&v)[R][8], float s, int d,
     *reinterpret_cast<uint4*>(o + c) = make_uint4(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]),
                                                   pack_bf16x2(y[4], y[5]), pack_bf16x2(y[6], y[7]));
   }
+}
+
+template <int R>
+__device__ __forceinline__ void layernorm_row_vec(const bf16* x, int d, float eps,
+                                                  const bf16* __restrict__ gain,
+                                                  const bf16* __restrict__ bias, bf16* o,
+                                                  int lane) {
+  float v[R][8];
+  const float s = layernorm_load<R>(x, d, lane, v);
+  const float2 st = layernorm_stats<R>(v, s, d, eps, lane);
+  layernorm_apply<R>(v, st.x, st.y, d, gain, bias, o, lane);
 }
 
 // 1/sqrt(mean(x^2) + eps) of one row of d elements, by one wave (every lane
@@ -308,6 +317,8 @@ struct GemmArgs {
   // 1/sqrt(mean(a^2) + row_eps) of its A row (formed by the GEMM) instead of
   // row_scale
   bool row_norm;
+  // bf16, at most 64 rows: which form (FewRows)
+  int few_rows;
   // bf16, where gemm_direct_fits holds: the GEMM makes its own row list (then
   // M_dev is the active count, A / A2 are read by token row) or clears a ticket;
   // nullable
@@ -337,6 +348,11 @@ struct RowList {
   unsigned long long* ticket;
 };
 constexpr int kDirectRows = 64;
+// GEMMs of at most 64 rows: one kernel (gemm_direct.hip) where gemm_direct_fits,
+// else the skinny path (with its workspace); the skinny path only; or one kernel
+// whose sums are the skinny path's bit for bit, where gemm_direct_split_fits.
+enum FewRows { kFewAny = 0, kFewSkinny = 1, kFewSplit = 2 };
+bool gemm_direct_split_fits(int M_max, int N, int K, int epi);
 // whether gemm() runs g as one kernel without a workspace (gemm_direct.hip)
 bool gemm_direct_fits(int M_max, int n_weights, int K, int epi);
 bool gemm_direct_fits(const GemmArgs& g);
@@ -368,7 +384,7 @@ struct ExitCompact {
   int cls_seq_len;
   uint8_t* key_live;
 };
-bool exit_compact_fits(const adept_exit_cfg& cfg, int d, int max_active);
+bool exit_compact_fits(const adept_exit_cfg& cfg, int d, int max_active, bool ln);
 adept_status exit_compact(const ExitCompact& x, hipStream_t s);
 // the argument checks of adept_compact
 adept_status compact_check(int layer, int n_layers, const uint8_t* exit_flag,

@@ -112,7 +112,8 @@ __global__ __launch_bounds__(256) void encoder_embed_vec_kernel(
       s += v[r][2 * e] + v[r][2 * e + 1];
     }
   }
-  layernorm_regs<R>(v, s, d, eps, g, b, out + (int64_t)j * d, lane);
+  const float2 st = layernorm_stats<R>(v, s, d, eps, lane);
+  layernorm_apply<R>(v, st.x, st.y, d, g, b, out + (int64_t)j * d, lane);
 }
 
 // Early stop of a sequence (the computation ends once the state that feeds
@@ -180,11 +181,14 @@ struct EncWs {
   size_t total;
 };
 
-// Whether all GEMMs of the step run as one kernel each (gemm_direct.hip)
+// Whether all GEMMs of the step run as one kernel each (gemm_direct.hip), with
+// the skinny path's sums: a sequence's states are the same whichever of the two
+// runs (see carve).
 bool step_direct(const adept_encoder_args* a) {
   const int dq = a->n_heads * a->head_dim, D = a->d_model, F = a->d_ff, n = a->n_tok;
-  return gemm_direct_fits(n, 3 * dq, D, EPI_QKV) && gemm_direct_fits(n, D, dq, EPI_RESID) &&
-         gemm_direct_fits(n, F, D, EPI_GELU) && gemm_direct_fits(n, D, F, EPI_RESID);
+  return gemm_direct_split_fits(n, 3 * dq, D, EPI_QKV) &&
+         gemm_direct_split_fits(n, D, dq, EPI_RESID) && gemm_direct_split_fits(n, F, D, EPI_GELU) &&
+         gemm_direct_split_fits(n, D, F, EPI_RESID);
 }
 
 EncWs carve(const adept_encoder_args* a, void* base) {
@@ -324,10 +328,13 @@ extern "C" adept_status adept_encoder_layer_step(const adept_encoder_args* a, in
   g.skinny_ws = ws.parts; g.skinny_ws_bytes = ws.parts_bytes;
   // few rows: LN2, the exit test, the early stop, the list update and the dead
   // keys are one kernel, whose two words the first GEMM clears
-  const bool tail = step_direct(a) && exit_compact_fits(a->exit, D, maxn);
+  const bool direct = step_direct(a);
+  const int few = direct ? kFewSplit : kFewSkinny;
+  const bool tail = direct && exit_compact_fits(a->exit, D, maxn, true);
   RowList list{};
   list.ticket = ws.ticket;
   if (tail) g.list = &list;
+  g.few_rows = few;
   ADEPT_TRY(gemm(ADEPT_BF16, g, s));
   // 2. bidirectional attention over the live rows of each sequence
   ADEPT_TRY(attend_dispatch(ADEPT_BF16, H, hd, 1.0f / sqrtf((float)hd), 0, a->q_buf, act, nact,
@@ -341,6 +348,7 @@ extern "C" adept_status adept_encoder_layer_step(const adept_encoder_args* a, in
   go.epi = EPI_RESID; go.bias = off(a->b_o, (int64_t)li * D);
   go.C = a->y_buf; go.ldc = D; go.resid = a->h[in]; go.rows = act; go.name = "enc_gemm_o";
   go.skinny_ws = ws.parts; go.skinny_ws_bytes = ws.parts_bytes;
+  go.few_rows = few;
   ADEPT_TRY(gemm(ADEPT_BF16, go, s));
   ADEPT_TRY(layernorm_rows(D, a->ln_eps, a->y_buf, act, nact, maxn, off(a->ln1_g, (int64_t)li * D),
                            off(a->ln1_b, (int64_t)li * D), a->y_buf, s));
@@ -351,6 +359,7 @@ extern "C" adept_status adept_encoder_layer_step(const adept_encoder_args* a, in
   gi.ldb = D; gi.epi = EPI_GELU; gi.bias = off(a->b_in, (int64_t)li * F);
   gi.C = a->ffn_act; gi.ldc = F; gi.name = "enc_gemm_in";
   gi.skinny_ws = ws.parts; gi.skinny_ws_bytes = ws.parts_bytes;
+  gi.few_rows = few;
   ADEPT_TRY(gemm(ADEPT_BF16, gi, s));
   // 5. h_out = LN2(h1 + a W_out^T + b_out)
   GemmArgs gu{};
@@ -359,6 +368,7 @@ extern "C" adept_status adept_encoder_layer_step(const adept_encoder_args* a, in
   gu.epi = EPI_RESID; gu.bias = off(a->b_out, (int64_t)li * D);
   gu.C = a->h[out]; gu.ldc = D; gu.resid = a->y_buf; gu.rows = act; gu.name = "enc_gemm_out";
   gu.skinny_ws = ws.parts; gu.skinny_ws_bytes = ws.parts_bytes;
+  gu.few_rows = few;
   ADEPT_TRY(gemm(ADEPT_BF16, gu, s));
   if (tail) {
     ExitCompact x{};

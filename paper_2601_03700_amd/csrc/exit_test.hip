@@ -227,7 +227,6 @@ constexpr int kSmallThreads = 256;
 
 template <int CH, bool LN>
 __global__ __launch_bounds__(kSmallThreads) void exit_compact_kernel(ExitParams p, SmallExit a) {
-  __shared__ float fs[4];
   __shared__ double ds[4][3];
   const int n = min(*a.n_active, a.max_active);
   const int k = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -253,26 +252,13 @@ __global__ __launch_bounds__(kSmallThreads) void exit_compact_kernel(ExitParams 
     for (int e = 0; e < 4; ++e) v[c][e] = bf2f(x[e]);
   }
   if constexpr (LN) {
-    auto block_sum = [&](float x) {
-      x = wave_sum_f32(x);
-      __syncthreads();
-      if (lane == 0) fs[wave] = x;
-      __syncthreads();
-      return (fs[0] + fs[1]) + (fs[2] + fs[3]);
-    };
-    float s = 0.0f;
-#pragma unroll
-    for (int c = 0; c < CH; ++c)
-      if (c * kSmallThreads + tid < nvec) s += (v[c][0] + v[c][1]) + (v[c][2] + v[c][3]);
-    const float mean = block_sum(s) / (float)p.d;
-    float qv = 0.0f;
-#pragma unroll
-    for (int c = 0; c < CH; ++c)
-      if (c * kSmallThreads + tid < nvec) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) qv = fmaf(v[c][e] - mean, v[c][e] - mean, qv);
-      }
-    const float r = 1.0f / sqrtf(block_sum(qv) / (float)p.d + a.ln_eps);
+    // every wave forms the row's statistics, with the sums of layernorm_row_vec
+    // (the LayerNorm of longer lists): the rows come out the same bit for bit
+    float w[2 * CH][8];
+    const float ls = layernorm_load<2 * CH>(hr, p.d, lane, w);
+    const float2 st = layernorm_stats<2 * CH>(w, ls, p.d, a.ln_eps, lane);
+    const float mean = st.x, r = st.y;
+    __syncthreads();   // the row has been read before it is normalised in place
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
       const int i = min(c * kSmallThreads + tid, nvec - 1);
@@ -500,9 +486,9 @@ extern "C" adept_status adept_exit_test(adept_dtype dt, int d_model, int layer,
 
 namespace adept {
 
-bool exit_compact_fits(const adept_exit_cfg& cfg, int d, int max_active) {
+bool exit_compact_fits(const adept_exit_cfg& cfg, int d, int max_active, bool ln) {
   return cfg.metric == ADEPT_SIM_GLOBAL && max_active > 0 && max_active <= 64 &&
-         d <= 8 * 4 * kSmallThreads;
+         d <= (ln ? 4 : 8) * 4 * kSmallThreads;
 }
 
 adept_status exit_compact(const ExitCompact& x, hipStream_t s) {
@@ -518,11 +504,17 @@ adept_status exit_compact(const ExitCompact& x, hipStream_t s) {
                     x.key_live};
   const dim3 grid(x.max_active), block(kSmallThreads);
   const int ch = ceil_div(x.d / 4, kSmallThreads);
-#define ADEPT_SMALL_CASE(C)                                                             do {                                                                                    if (x.ln_g)                                                                             ADEPT_LAUNCH((exit_compact_kernel<C, true>), grid, block, 0, s, p, a);              else                                                                                    ADEPT_LAUNCH((exit_compact_kernel<C, false>), grid, block, 0, s, p, a);           } while (0)
+#define ADEPT_SMALL_CASE(C)                                                             \
+  do {                                                                                  \
+    if (x.ln_g)                                                                         \
+      ADEPT_LAUNCH((exit_compact_kernel<C, true>), grid, block, 0, s, p, a);            \
+    else                                                                                \
+      ADEPT_LAUNCH((exit_compact_kernel<C, false>), grid, block, 0, s, p, a);           \
+  } while (0)
   if (ch <= 1) ADEPT_SMALL_CASE(1);
   else if (ch <= 2) ADEPT_SMALL_CASE(2);
   else if (ch <= 4) ADEPT_SMALL_CASE(4);
-  else ADEPT_SMALL_CASE(8);
+  else ADEPT_LAUNCH((exit_compact_kernel<8, false>), grid, block, 0, s, p, a);   // no LN: _fits
 #undef ADEPT_SMALL_CASE
   return launch_status("exit_compact");
 }

@@ -139,34 +139,10 @@ adept_status launch_bf16(const GP& p, hipStream_t s, const char* name) {
 // order (deterministic) and applies the same epilogues as the tiled path.
 // ---------------------------------------------------------------------------
 constexpr int kSkinnyM = 64;      // rows of a skinny pass (decode: one per sequence)
-constexpr int kSkinnyBN = 64;     // output columns per tile
 constexpr int kSkStages = 4;      // LDS ring depth
 constexpr int kSkStage = 2 * 64 * 128;   // A and B, 64 rows x 64 k each: 16 KiB
 constexpr int kSkPart = kSkinnyM * kSkinnyBN;   // floats of one partial tile
 constexpr int kSkGroups = 512;    // target grid: two workgroups per CU
-
-struct SkSplit {
-  int G;        // workgroups
-  int U;        // units per workgroup (the last one may hold fewer)
-  int KT;       // k steps per tile
-  int64_t total;
-};
-
-SkSplit skinny_split(int Nt, int K) {
-  SkSplit sp;
-  sp.KT = K / BK;
-  sp.total = (int64_t)(Nt / kSkinnyBN) * sp.KT;
-  if (sp.total <= 0) {   // no work (the entry rejects K or N below one tile)
-    sp.G = 0;
-    sp.U = 1;
-    return sp;
-  }
-  const int64_t g = std::max<int64_t>(1, std::min<int64_t>(kSkGroups, sp.total));
-  // at least four k steps (32 KiB of weights) against each 16 KiB partial tile
-  sp.U = (int)std::min<int64_t>(std::max<int64_t>((sp.total + g - 1) / g, 4), sp.KT);
-  sp.G = (int)((sp.total + sp.U - 1) / sp.U);
-  return sp;
-}
 
 // Skinny GEMM (M <= 64): workgroup w multiplies the units [w*U, w*U + U) and
 // writes the partial tile of each segment to part[w][segment][m][c].  The
@@ -465,6 +441,22 @@ bool aligned_operands(const GemmArgs& g) {
 }
 
 }  // namespace
+
+SkSplit skinny_split(int Nt, int K) {
+  SkSplit sp;
+  sp.KT = K / BK;
+  sp.total = (int64_t)(Nt / kSkinnyBN) * sp.KT;
+  if (sp.total <= 0) {   // no work (the entry rejects K or N below one tile)
+    sp.G = 0;
+    sp.U = 1;
+    return sp;
+  }
+  const int64_t g = std::max<int64_t>(1, std::min<int64_t>(kSkGroups, sp.total));
+  // at least four k steps (32 KiB of weights) against each 16 KiB partial tile
+  sp.U = (int)std::min<int64_t>(std::max<int64_t>((sp.total + g - 1) / g, 4), sp.KT);
+  sp.G = (int)((sp.total + sp.U - 1) / sp.U);
+  return sp;
+}
 
 size_t skinny_ws_bytes(int Nt, int K) {
   return (size_t)skinny_split(Nt, K).G * 2 * kSkPart * sizeof(float);

@@ -40,10 +40,15 @@ struct DirPre {
 
 // NB == 1 with a pair epilogue (rotary halves, gate and up): the 16 rows of the
 // block are 8 of the first kind and their 8 partners.
-template <int EPI, int NB, int MB, int W, int U>
-__global__ __launch_bounds__(64 * W) void gemm_direct_kernel(GP p, RowList rl, int row_norm) {
+//
+// SPLIT: the sums in the order of the skinny path (gemm.hip), bit for bit: K in
+// the segments its split sp gives these columns' tile, each one chain from zero,
+// added up in ascending order.  The waves take every eighth segment.
+template <int EPI, int NB, int MB, int W, int U, bool SPLIT>
+__global__ __launch_bounds__(64 * W) void gemm_direct_kernel(GP p, RowList rl, int row_norm,
+                                                             SkSplit sp) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  float4* red = reinterpret_cast<float4*>(smem);      // [wave][MB * NB][64]
+  float4* red = reinterpret_cast<float4*>(smem);      // [wave or segment][MB * NB][64]
   __shared__ float ssq[W][MB * 16];
   __shared__ int32_t list[64];
   __shared__ uint8_t from2[64];
@@ -86,6 +91,12 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(GP p, RowList rl, i
       act = rl.act[lane];
     }
   }
+  // SPLIT: the segments of K, numbered from sp's first workgroup of the tile that
+  // holds these columns
+  [[maybe_unused]] const int u0 = SPLIT ? n0 / kSkinnyBN * KT : 0, w0 = SPLIT ? u0 / sp.U : 0;
+  const int nseg = SPLIT ? (u0 + KT - 1) / sp.U - w0 + 1 : W;
+  auto lo_of = [&](int s) { return max((w0 + s) * sp.U - u0, 0); };
+  auto hi_of = [&](int s) { return min((w0 + s + 1) * sp.U - u0, KT); };
   const bf16* br[NB];
   {
     const bool two = NB == 1 && pair && r16 >= 8;   // a lane of the second kind
@@ -97,13 +108,13 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(GP p, RowList rl, i
                                  : p.B + (int64_t)(n0 + dn + r16) * p.ldb) + 8 * q;
   }
   u32x4_t bw[2][U][NB][2], aw[2][U][MB][2];
-  const int mine = KT > wave ? (KT - wave + W - 1) / W : 0;   // this wave's pieces of K
-  const int iters = (mine + U - 1) / U;
-  auto load_b = [&](int it, u32x4_t (&b)[U][NB][2]) {
+  // a stage: up to U pieces of K from c0 on, below hi
+  constexpr int kStep = SPLIT ? 1 : W;
+  auto load_b = [&](int c0, int hi, u32x4_t (&b)[U][NB][2]) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int c = (it * U + u) * W + wave;
-      if (c >= KT) continue;   // uniform over the wave
+      const int c = c0 + u * kStep;
+      if (c >= hi) continue;   // uniform over the wave
 #pragma unroll
       for (int x = 0; x < NB; ++x)
 #pragma unroll
@@ -112,7 +123,11 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(GP p, RowList rl, i
               reinterpret_cast<const u32x4_t*>(br[x] + (int64_t)c * BK + 32 * h));
     }
   };
-  load_b(0, bw[0]);
+  if constexpr (SPLIT) {
+    if (wave < nseg) load_b(lo_of(wave), hi_of(wave), bw[0]);
+  } else {
+    load_b(wave, KT, bw[0]);
+  }
 
   // the rows: active rows, then (row list) the rows that exited before the
   // layer, in one ballot of at most 64 token rows
@@ -156,11 +171,11 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(GP p, RowList rl, i
     for (int i = 0; i < G; ++i)
       if (pre[i].m >= M) pre[i].row = 0;
   }
-  auto load_a = [&](int it, u32x4_t (&a)[U][MB][2]) {
+  auto load_a = [&](int c0, int hi, u32x4_t (&a)[U][MB][2]) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int c = (it * U + u) * W + wave;
-      if (c >= KT) continue;
+      const int c = c0 + u * kStep;
+      if (c >= hi) continue;
 #pragma unroll
       for (int y = 0; y < MB; ++y)
         if (y == 0 || 16 * y < M) {
@@ -170,7 +185,11 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(GP p, RowList rl, i
         }
     }
   };
-  load_a(0, aw[0]);
+  if constexpr (SPLIT) {
+    if (wave < nseg) load_a(lo_of(wave), hi_of(wave), aw[0]);
+  } else {
+    load_a(wave, KT, aw[0]);
+  }
   // the epilogue's inputs
 #pragma unroll
   for (int i = 0; i < G; ++i) {
@@ -203,10 +222,10 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(GP p, RowList rl, i
 #pragma unroll
     for (int x = 0; x < NB; ++x) acc[y][x] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   }
-  auto step = [&](int it, u32x4_t (&a)[U][MB][2], u32x4_t (&b)[U][NB][2]) {
+  auto step = [&](int c0, int hi, u32x4_t (&a)[U][MB][2], u32x4_t (&b)[U][NB][2]) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if ((it * U + u) * W + wave >= KT) continue;
+      if (c0 + u * kStep >= hi) continue;
 #pragma unroll
       for (int y = 0; y < MB; ++y)
         if (y == 0 || 16 * y < M) {
@@ -230,28 +249,76 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(GP p, RowList rl, i
         }
     }
   };
-#pragma unroll 1
-  for (int it = 0; it < iters; it += 2) {
-    if (it + 1 < iters) {
-      load_b(it + 1, bw[1]);
-      load_a(it + 1, aw[1]);
-    }
-    step(it, aw[0], bw[0]);
-    if (it + 1 < iters) {
-      if (it + 2 < iters) {
-        load_b(it + 2, bw[0]);
-        load_a(it + 2, aw[0]);
+  auto hand_over = [&](int s) {   // the sums of segment s
+#pragma unroll
+    for (int y = 0; y < MB; ++y)
+#pragma unroll
+      for (int x = 0; x < NB; ++x)
+        red[(s * MB * NB + y * NB + x) * 64 + lane] =
+            make_float4(acc[y][x][0], acc[y][x][1], acc[y][x][2], acc[y][x][3]);
+  };
+  if constexpr (SPLIT) {
+    // stage (s, c): pieces c.. of segment s; the next one may open the wave's
+    // next segment, whose loads then pass the hand-over
+    auto next = [&](int& s, int& c) {
+      c += U;
+      if (c >= hi_of(s)) {
+        s += W;
+        c = lo_of(s);
       }
-      step(it + 1, aw[1], bw[1]);
+    };
+    auto finish = [&](int s) {
+      hand_over(s);
+#pragma unroll
+      for (int y = 0; y < MB; ++y)
+#pragma unroll
+        for (int x = 0; x < NB; ++x) acc[y][x] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    };
+    int s = wave, c = lo_of(wave);
+#pragma unroll 1
+    while (s < nseg) {
+      int s1 = s, c1 = c;
+      next(s1, c1);
+      if (s1 < nseg) {
+        load_b(c1, hi_of(s1), bw[1]);
+        load_a(c1, hi_of(s1), aw[1]);
+      }
+      step(c, hi_of(s), aw[0], bw[0]);
+      if (s1 != s) finish(s);
+      s = s1;
+      c = c1;
+      if (s >= nseg) break;
+      next(s1, c1);
+      if (s1 < nseg) {
+        load_b(c1, hi_of(s1), bw[0]);
+        load_a(c1, hi_of(s1), aw[0]);
+      }
+      step(c, hi_of(s), aw[1], bw[1]);
+      if (s1 != s) finish(s);
+      s = s1;
+      c = c1;
     }
+  } else {
+    const int mine = KT > wave ? (KT - wave + W - 1) / W : 0;   // this wave's pieces of K
+    const int iters = (mine + U - 1) / U;
+    auto at = [&](int it) { return it * U * W + wave; };
+#pragma unroll 1
+    for (int it = 0; it < iters; it += 2) {
+      if (it + 1 < iters) {
+        load_b(at(it + 1), KT, bw[1]);
+        load_a(at(it + 1), KT, aw[1]);
+      }
+      step(at(it), KT, aw[0], bw[0]);
+      if (it + 1 < iters) {
+        if (it + 2 < iters) {
+          load_b(at(it + 2), KT, bw[0]);
+          load_a(at(it + 2), KT, aw[0]);
+        }
+        step(at(it + 1), KT, aw[1], bw[1]);
+      }
+    }
+    hand_over(wave);   // a wave without pieces: zeros
   }
-  // a wave without pieces hands over zeros
-#pragma unroll
-  for (int y = 0; y < MB; ++y)
-#pragma unroll
-    for (int x = 0; x < NB; ++x)
-      red[(wave * MB * NB + y * NB + x) * 64 + lane] =
-          make_float4(acc[y][x][0], acc[y][x][1], acc[y][x][2], acc[y][x][3]);
   if (row_norm) {
 #pragma unroll
     for (int y = 0; y < MB; ++y) {
@@ -264,11 +331,17 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(GP p, RowList rl, i
   __syncthreads();
   // lane l of block (y, x): row 16 y + l % 16, four columns by l / 16
   auto sum = [&](int blk, int l) {
-    float4 t = red[blk * 64 + l];
-#pragma unroll
-    for (int w = 1; w < W; ++w) {
+    float4 t = SPLIT ? make_float4(0.f, 0.f, 0.f, 0.f) : red[blk * 64 + l];
+    auto add = [&](int w) {
       const float4 o = red[(w * MB * NB + blk) * 64 + l];
       t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
+    };
+    if constexpr (SPLIT) {
+#pragma unroll 4
+      for (int w = 0; w < nseg; ++w) add(w);
+    } else {
+#pragma unroll
+      for (int w = 1; w < W; ++w) add(w);
     }
     return t;
   };
@@ -331,40 +404,60 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(GP p, RowList rl, i
   }
 }
 
-template <int EPI, int NB, int MB, int W, int U>
+// LDS of a SPLIT workgroup's sums: at most this (beside the static arrays)
+constexpr size_t kSplitLds = 128 * 1024;
+// the most segments a tile has
+int split_segments(const SkSplit& sp) {
+  return sp.KT % sp.U == 0 ? sp.KT / sp.U : (sp.KT + sp.U - 2) / sp.U + 1;
+}
+
+template <int EPI, int NB, int MB, int W, int U, bool SPLIT>
 adept_status dir_launch(const GP& p, const RowList& rl, int row_norm, const char* name,
                         hipStream_t s) {
-  constexpr int kRed = W * MB * NB * 1024;
+  SkSplit sp{};
+  int parts = W;
+  if (SPLIT) {
+    sp = skinny_split(p.N, p.K);
+    parts = split_segments(sp);
+  }
+  const size_t red = (size_t)parts * MB * NB * 1024;
   static bool attr_set = false;
-  if (kRed > 48 * 1024)
-    ADEPT_TRY(lds_limit((const void*)gemm_direct_kernel<EPI, NB, MB, W, U>, kRed, &attr_set,
-                        "gemm_direct LDS limit"));
+  if (SPLIT || red > 48 * 1024)
+    ADEPT_TRY(lds_limit((const void*)gemm_direct_kernel<EPI, NB, MB, W, U, SPLIT>,
+                        SPLIT ? kSplitLds : red, &attr_set, "gemm_direct LDS limit"));
   const int cols = EPI == EPI_SWIGLU ? 8 * NB : 16 * NB;
   {
     TimedLaunch tl(name ? name : "gemm_direct", s);
-    hipLaunchKernelGGL((gemm_direct_kernel<EPI, NB, MB, W, U>), dim3(p.N / cols), dim3(64 * W), kRed,
-                       s, p, rl, row_norm);
+    hipLaunchKernelGGL((gemm_direct_kernel<EPI, NB, MB, W, U, SPLIT>), dim3(p.N / cols),
+                       dim3(64 * W), red, s, p, rl, row_norm, sp);
   }
   return launch_status("gemm_direct");
 }
 
-template <int EPI>
+// 32 weight rows per workgroup where they still give half the chip one: the
+// activations are read half as often (24 rows, width 1600: QKV 14.0 -> 11.0 us
+// with 150 workgroups, but the O and down projections 12.4 -> 18.1 with 50)
+bool dir_wide(int N, int epi) { return (epi == EPI_SWIGLU ? N / 16 : N / 32) >= 128; }
+
+template <int EPI, bool SPLIT>
 adept_status dir_rows(const GP& p, const RowList& rl, int row_norm, const char* name,
                       hipStream_t s) {
   const int M = rl.exit_layer ? rl.n_tok : p.M_max;
   // one piece of K in flight per stage for QKV, whose workgroups (768 of them at
   // the 7B width) are short and start with the row list: more of them per CU
-  // (28 -> 24 us); two for the others (down and O projections 18 -> 15.6)
-  if (M <= 16) return dir_launch<EPI, 1, 1, 8, EPI == EPI_QKV ? 1 : 2>(p, rl, row_norm, name, s);
-  // 32 weight rows per workgroup where they still give half the chip one: the
-  // activations are read half as often (24 rows, width 1600: QKV 14.0 -> 11.0 us
-  // with 150 workgroups, but the O and down projections 12.4 -> 18.1 with 50)
-  const bool wide = (EPI == EPI_SWIGLU ? p.N / 16 : p.N / 32) >= 128;
+  // (28 -> 24 us); two for the others (down and O projections 18 -> 15.6).
+  // SPLIT: a wave's segment is four pieces at least and few waves have one (three
+  // at K = 768), so its loads are issued together (twelve layers of width 768:
+  // 12 rows 524 -> 500 us, 40 rows 687 -> 661)
+  if (M <= 16)
+    return dir_launch<EPI, 1, 1, 8, SPLIT ? 4 : EPI == EPI_QKV ? 1 : 2, SPLIT>(p, rl, row_norm, name,
+                                                                               s);
+  const bool wide = dir_wide(p.N, EPI);
   if (M <= 32)
-    return wide ? dir_launch<EPI, 2, 2, 8, 2>(p, rl, row_norm, name, s)
-                : dir_launch<EPI, 1, 2, 8, 2>(p, rl, row_norm, name, s);
-  return wide ? dir_launch<EPI, 2, 4, 8, 1>(p, rl, row_norm, name, s)
-              : dir_launch<EPI, 1, 4, 8, 1>(p, rl, row_norm, name, s);
+    return wide ? dir_launch<EPI, 2, 2, 8, 2, SPLIT>(p, rl, row_norm, name, s)
+                : dir_launch<EPI, 1, 2, 8, SPLIT ? 4 : 2, SPLIT>(p, rl, row_norm, name, s);
+  return wide ? dir_launch<EPI, 2, 4, 8, 1, SPLIT>(p, rl, row_norm, name, s)
+              : dir_launch<EPI, 1, 4, 8, SPLIT ? 2 : 1, SPLIT>(p, rl, row_norm, name, s);
 }
 
 }  // namespace
@@ -385,7 +478,16 @@ bool gemm_direct_fits(int M_max, int n_weights, int K, int epi) {
          (narrow || (M_max <= 16 && epi != EPI_STORE));
 }
 
+bool gemm_direct_split_fits(int M_max, int N, int K, int epi) {
+  if (epi == EPI_SWIGLU || !gemm_direct_fits(M_max, N, K, epi) || N % kSkinnyBN != 0) return false;
+  const SkSplit sp = skinny_split(N, K);
+  const int mb = M_max <= 16 ? 1 : M_max <= 32 ? 2 : 4, nb = M_max > 16 && dir_wide(N, epi) ? 2 : 1;
+  return sp.G > 0 && (size_t)split_segments(sp) * mb * nb * 1024 <= kSplitLds;
+}
+
 bool gemm_direct_fits(const GemmArgs& g) {
+  if (g.few_rows == kFewSkinny) return false;
+  if (g.few_rows == kFewSplit) return !g.rope_cos && gemm_direct_split_fits(g.M_max, g.N, g.K, g.epi);
   return gemm_direct_fits(g.M_max, g.epi == EPI_SWIGLU ? 2 * g.N : g.N, g.K, g.epi);
 }
 
@@ -393,13 +495,23 @@ adept_status gemm_direct(const GemmArgs& g, hipStream_t s) {
   const GP p = to_gp(g);
   const RowList rl = g.list ? *g.list : RowList{};
   const int rn = g.row_norm ? 1 : 0;
+  if (g.few_rows == kFewSplit) {
+    switch (g.epi) {
+      case EPI_QKV: return dir_rows<EPI_QKV, true>(p, rl, rn, g.name, s);
+      case EPI_RESID: return dir_rows<EPI_RESID, true>(p, rl, rn, g.name, s);
+      case EPI_GELU: return dir_rows<EPI_GELU, true>(p, rl, rn, g.name, s);
+      default: break;
+    }
+    set_error("gemm: few_rows = split without this epilogue");
+    return ADEPT_E_INVALID;
+  }
   switch (g.epi) {
-    case EPI_STORE: return dir_rows<EPI_STORE>(p, rl, rn, g.name, s);
-    case EPI_QKV: return dir_rows<EPI_QKV>(p, rl, rn, g.name, s);
-    case EPI_RESID: return dir_rows<EPI_RESID>(p, rl, rn, g.name, s);
-    case EPI_SWIGLU: return dir_rows<EPI_SWIGLU>(p, rl, rn, g.name, s);
-    case EPI_GELU: return dir_rows<EPI_GELU>(p, rl, rn, g.name, s);
-    case EPI_GELU_TANH: return dir_rows<EPI_GELU_TANH>(p, rl, rn, g.name, s);
+    case EPI_STORE: return dir_rows<EPI_STORE, false>(p, rl, rn, g.name, s);
+    case EPI_QKV: return dir_rows<EPI_QKV, false>(p, rl, rn, g.name, s);
+    case EPI_RESID: return dir_rows<EPI_RESID, false>(p, rl, rn, g.name, s);
+    case EPI_SWIGLU: return dir_rows<EPI_SWIGLU, false>(p, rl, rn, g.name, s);
+    case EPI_GELU: return dir_rows<EPI_GELU, false>(p, rl, rn, g.name, s);
+    case EPI_GELU_TANH: return dir_rows<EPI_GELU_TANH, false>(p, rl, rn, g.name, s);
     default: set_error("gemm: bad epilogue"); return ADEPT_E_INVALID;
   }
 }

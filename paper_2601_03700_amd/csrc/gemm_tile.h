@@ -1033,6 +1033,17 @@ inline adept_status lds_limit(const void* kernel, size_t bytes, bool* done, cons
   return ADEPT_OK;
 }
 
+// The skinny path's cut of the weights (gemm.hip): units of one 64-column tile
+// times one 64-deep k step, in equal contiguous ranges, one per workgroup.
+constexpr int kSkinnyBN = 64;     // output columns per tile
+struct SkSplit {
+  int G;        // workgroups
+  int U;        // units per workgroup (the last one may hold fewer)
+  int KT;       // k steps per tile
+  int64_t total;
+};
+SkSplit skinny_split(int Nt, int K);
+
 // The smaller tiles.  mid_choose: which tile the GEMM takes; gemm_mid_128x256
 // and gemm_mid_128x128 run it, cutting tiles along K into the workspace when
 // it has mid_ws_bytes.

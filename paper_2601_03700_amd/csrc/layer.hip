@@ -327,7 +327,7 @@ extern "C" adept_status adept_layer_step(const adept_layer_args* a, int layer, v
   const int32_t* nq = nact;
   const int qmax = fused ? a->n_tok : maxn;
   const bool direct = step_direct(a);
-  const bool tail = direct && exit_compact_fits(a->exit, D, maxn) && a->exit.prompt_level == 0;
+  const bool tail = direct && exit_compact_fits(a->exit, D, maxn, false) && a->exit.prompt_level == 0;
   // fused schedule: the row list and the QKV rows' norm (the RMSNorm
   // factors, or the LayerNorm rows when they fit one wave's registers) come
   // from one kernel, or from the GEMM itself (RMSNorm family, direct)

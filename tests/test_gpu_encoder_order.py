@@ -19,6 +19,12 @@ DEV = "cuda"
 
 BASE = ai.EncoderShape(n_layers=3, d_model=768, n_heads=12, head_dim=64, d_ff=3072, vocab=500,
                        max_pos=512)
+# one kernel per GEMM up to 40 rows, the skinny path from 41 on: K in whole segments of
+# the split (16 and 64 pieces, four each) and in ragged ones (13 and 52 pieces)
+LARGE = ai.EncoderShape(n_layers=3, d_model=1024, n_heads=16, head_dim=64, d_ff=4096, vocab=500,
+                        max_pos=512)
+RAGGED = ai.EncoderShape(n_layers=3, d_model=832, n_heads=13, head_dim=64, d_ff=3328, vocab=500,
+                         max_pos=512)
 
 
 def _final(model, shape, ids, force):
@@ -50,3 +56,10 @@ def _same_alone_and_beside(shape, length, counts):
 @pytest.mark.parametrize("length,counts", [(70, (1, 2, 58)), (129, (1, 5, 30)), (300, (1, 8, 20))])
 def test_more_than_64_rows(length, counts):
     _same_alone_and_beside(BASE, length, counts)
+
+
+@pytest.mark.parametrize("shape,length,counts", [(LARGE, 12, (1, 2, 3, 5)), (LARGE, 20, (1, 2, 3)),
+                                                 (RAGGED, 12, (1, 2, 3, 5)), (RAGGED, 20, (1, 2, 3)),
+                                                 (RAGGED, 1, (1, 16, 17, 64))])
+def test_up_to_64_rows(shape, length, counts):
+    _same_alone_and_beside(shape, length, counts)
