@@ -159,12 +159,15 @@ __device__ __forceinline__ float silu(float g) {
   return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g));
 }
 
-// x * Phi(x), the normal CDF from Phi(-a) = t P(t) exp(-a^2/2), a = |x|,
-// t = 1/(1 + 0.21213203f a): P fits exp(a^2/2) Phi(-a) / t over a = 0..13.5 to 2e-8
-// relative (least squares weighted towards the largest error), so the result
-// is as exact as f32 in the whole range, also where 1 + erf would cancel.
-// One branch-free polynomial: the two-branch erff took 110 of the 270 us of a
-// 32768 x 3072 GELU projection.
+// x * Phi(x) rounded to bf16, where Phi is formed by 1 + erff: the same bits for
+// every x, mostly without erff.  The normal CDF from Phi(-a) = t P(t) exp(-a^2/2),
+// a = |x|, t = 1/(1 + 0.21213203f a), where P fits exp(a^2/2) Phi(-a) / t over
+// a = 0..13.5 to 4.5e-8 relative (least squares weighted towards the largest
+// error), is within kGeluErr a of the form with erff, so where both ends of that
+// interval round to the same bf16 that is the result; erff decides the others
+// (6e-4 of the values in (-1, 0), 3e-3 in (-2, -1), 4e-2 in (-3, -2)).  The two-branch erff took 110 of the
+// 270 us of a 32768 x 3072 GELU projection.
+constexpr float kGeluErr = 4.5e-7f;   // the largest over all floats: 2.98e-7
 __device__ __forceinline__ float gelu_erf(float x) {
   const float a = fabsf(x);
   const float t = __builtin_amdgcn_rcpf(fmaf(0.2121320366859436f, a, 1.0f));
@@ -178,7 +181,12 @@ __device__ __forceinline__ float gelu_erf(float x) {
   q = fmaf(q, t, 0.08534912019968033f);
   q = fmaf(q, t, 0.08459459245204926f);
   const float h = t * q * __expf(-0.5f * a * a);   // Phi(-a)
-  return x * (x < 0.0f ? h : 1.0f - h);
+  const float y = x * (x < 0.0f ? h : 1.0f - h), e = kGeluErr * a;
+  const uint32_t w = pack_bf16x2(y - e, y + e);
+  float r = __uint_as_float(w << 16);
+  if ((w ^ (w << 16)) >> 16)   // NaN too
+    r = bf2f(f2bf(0.5f * x * (1.0f + erff(x * 0.7071067811865476f))));
+  return r;
 }
 
 // x * Phi(x) with the tanh approximation of the normal CDF (GPT-2's MLP):

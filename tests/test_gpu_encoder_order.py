@@ -63,3 +63,26 @@ def test_more_than_64_rows(length, counts):
                                                  (RAGGED, 1, (1, 16, 17, 64))])
 def test_up_to_64_rows(shape, length, counts):
     _same_alone_and_beside(shape, length, counts)
+
+
+@pytest.mark.parametrize("rows", [1, 20, 40, 48, 200])   # one kernel, skinny, tiles
+def test_gelu_of_every_bf16(rows):
+    """The GELU epilogues' bits are those of the form with erff, for every bf16 value
+    (with no input weights the bias is the argument)."""
+    print(f"gelu rows={rows}", flush=True)
+    shape = ai.EncoderShape(n_layers=8, d_model=640, n_heads=10, head_dim=64, d_ff=8192, vocab=50,
+                            max_pos=512)
+    w = ai.encoder_weights(shape, seed=1, dtype="bf16")
+    x = torch.arange(65536, dtype=torch.int32).to(torch.int16).view(torch.bfloat16).float()
+    x = x[torch.argsort(x.abs().nan_to_num(math.inf, math.inf))].view(8, 8192)
+    assert not x[:7].isinf().any() and not x[:7].isnan().any()   # the states stay finite
+    for lw, b in zip(w["layers"], x):
+        lw["w_in"], lw["b_in"] = np.zeros_like(lw["w_in"]), b.numpy()
+        lw["w_out"] = np.zeros_like(lw["w_out"])
+    seen = []
+    EncoderModel(shape, w).classify(ai.token_ids(1, shape.vocab, 1, rows),
+                                    B.exit_cfg(math.inf, shape.n_layers),
+                                    on_layer=lambda i, st: seen.append(st["ffn_act"].clone()))
+    for b, got in zip(x.to(DEV), seen):
+        want = (0.5 * b * (1.0 + torch.erf(b * 0.7071067811865476))).to(torch.bfloat16)
+        assert torch.equal(got.nan_to_num(7.0), want.nan_to_num(7.0).expand_as(got))
