@@ -74,23 +74,25 @@ __global__ __launch_bounds__(256) void encoder_embed_kernel(
   for (int c = lane; c < d; c += 64) o[c] = f2bf((val(c) - mean) * r * bf2f(g[c]) + bf2f(b[c]));
 }
 
-// The same with the row in registers (lane l: the 8-element chunks l, l+64,
-// ...; d a multiple of 8 up to 512 R): every table row is read once, by
-// 16-byte loads.  32768 rows of 768: 70 us element by element over three
-// passes, 24 so.
+// The same, bit for bit, with the row in registers (lane l: the 8-element chunks
+// l, l+64, ...; d a multiple of 8 up to 512 R): every table row is read once, by
+// 16-byte loads.  The sums are those of the kernel above, in which lane l adds up
+// the elements l, l+64, ...: the row passes through LDS for them.  32768 rows of
+// 768: 70 us element by element over three passes, 24 so.
 template <int R>
 __global__ __launch_bounds__(256) void encoder_embed_vec_kernel(
     int n, int d, int vocab, int max_pos, float eps, const int32_t* __restrict__ ids,
     const int32_t* __restrict__ pos, const bf16* __restrict__ word, const bf16* __restrict__ pemb,
     const bf16* __restrict__ temb, const bf16* __restrict__ g, const bf16* __restrict__ b,
     bf16* __restrict__ out) {
+  __shared__ float4 sm[4][R * 128];   // a row per wave
   const int lane = threadIdx.x & 63;
   const int j = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (j >= n) return;
+  if (j >= n) return;   // the whole wave: no barrier below spans waves
   const int64_t id = min(max(ids[j], 0), vocab - 1);
   const int64_t p = min(max(pos[j], 0), max_pos - 1);
+  float4* row = sm[threadIdx.x >> 6];
   float v[R][8];
-  float s = 0.0f;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int c = (lane + 64 * r) * 8;
@@ -109,11 +111,24 @@ __global__ __launch_bounds__(256) void encoder_embed_vec_kernel(
       v[r][2 * e + 1] = __uint_as_float(uw[e] & 0xffff0000u) +
                         __uint_as_float(uq[e] & 0xffff0000u) +
                         __uint_as_float(ut[e] & 0xffff0000u);
-      s += v[r][2 * e] + v[r][2 * e + 1];
     }
+    row[2 * (lane + 64 * r)] = make_float4(v[r][0], v[r][1], v[r][2], v[r][3]);
+    row[2 * (lane + 64 * r) + 1] = make_float4(v[r][4], v[r][5], v[r][6], v[r][7]);
   }
-  const float2 st = layernorm_stats<R>(v, s, d, eps, lane);
-  layernorm_apply<R>(v, st.x, st.y, d, g, b, out + (int64_t)j * d, lane);
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  const float* x = reinterpret_cast<const float*>(row);
+  float s = 0.0f;
+  for (int c = lane; c < d; c += 64) s += x[c];
+  const float mean = wave_sum_f32(s) / (float)d;
+  float q = 0.0f;
+  for (int c = lane; c < d; c += 64) {
+    const float t = x[c] - mean;
+    q = fmaf(t, t, q);
+  }
+  const float rs = 1.0f / sqrtf(wave_sum_f32(q) / (float)d + eps);
+  layernorm_apply<R>(v, mean, rs, d, g, b, out + (int64_t)j * d, lane);
 }
 
 // Early stop of a sequence (the computation ends once the state that feeds
