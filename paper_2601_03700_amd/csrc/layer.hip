@@ -326,7 +326,11 @@ extern "C" adept_status adept_layer_step(const adept_layer_args* a, int layer, v
   const int32_t* qrows = act;         // rows of the QKV GEMM
   const int32_t* nq = nact;
   const int qmax = fused ? a->n_tok : maxn;
+  // at most 64 rows: all GEMMs of the step direct, or all on the skinny path, whose
+  // epilogues carry the next norm and the exit test (width 512, MLP 4096, 64
+  // rows, only the gate/up projection skinny: 132 us two layers, all 119)
   const bool direct = step_direct(a);
+  const int few = direct ? kFewAny : kFewSkinny;
   const bool tail = direct && exit_compact_fits(a->exit, D, maxn, false) && a->exit.prompt_level == 0;
   // fused schedule: the row list and the QKV rows' norm (the RMSNorm
   // factors, or the LayerNorm rows when they fit one wave's registers) come
@@ -402,6 +406,7 @@ extern "C" adept_status adept_layer_step(const adept_layer_args* a, int layer, v
     g.rows = qrows; g.pos = a->pos; g.slot = a->slot; g.head_dim = hd; g.d_q = dq;
     g.q_out = a->q_buf; g.k_cache = kc; g.v_cache = vc; g.name = "gemm_qkv";
     g.skinny_ws = ws.skinny; g.skinny_ws_bytes = ws.skinny_bytes;
+    g.few_rows = few;
     if (tail) g.list = &list;
     ADEPT_TRY(gemm(dt, g, s));
     // 3. attention over the mixed cache
@@ -415,6 +420,7 @@ extern "C" adept_status adept_layer_step(const adept_layer_args* a, int layer, v
     go.bias = off(a->b_o, li * D);
     go.C = a->h[out]; go.ldc = D; go.resid = a->h[in]; go.rows = act; go.name = "gemm_o";
     go.skinny_ws = ws.skinny; go.skinny_ws_bytes = ws.skinny_bytes;
+    go.few_rows = few;
     // 5. LN2: on the skinny path the projection's epilogue writes it
     if (gemm_skinny_row_norm(go)) {
       go.ln_out = ws.xnorm;
@@ -431,6 +437,7 @@ extern "C" adept_status adept_layer_step(const adept_layer_args* a, int layer, v
     gf.bias = off(a->b_fc, li * F);
     gf.C = a->ffn_act; gf.ldc = F; gf.name = "gemm_fc";
     gf.skinny_ws = ws.skinny; gf.skinny_ws_bytes = ws.skinny_bytes;
+    gf.few_rows = few;
     ADEPT_TRY(gemm(dt, gf, s));
     // 7. second MLP projection + bias + residual (in place on h[out])
     GemmArgs gd{};
@@ -439,6 +446,7 @@ extern "C" adept_status adept_layer_step(const adept_layer_args* a, int layer, v
     gd.bias = off(a->b_proj, li * D);
     gd.C = a->h[out]; gd.ldc = D; gd.resid = a->h[out]; gd.rows = act; gd.name = "gemm_proj";
     gd.skinny_ws = ws.skinny; gd.skinny_ws_bytes = ws.skinny_bytes;
+    gd.few_rows = few;
     ADEPT_TRY(exit_in_epilogue(gd));
     ADEPT_TRY(gemm(dt, gd, s));
   } else if (qmax > 0) {
@@ -466,6 +474,7 @@ extern "C" adept_status adept_layer_step(const adept_layer_args* a, int layer, v
     g.rope_cos = a->rope_cos; g.rope_sin = a->rope_sin; g.head_dim = hd; g.d_q = dq;
     g.q_out = a->q_buf; g.k_cache = kc; g.v_cache = vc; g.name = "gemm_qkv";
     g.skinny_ws = ws.skinny; g.skinny_ws_bytes = ws.skinny_bytes;
+    g.few_rows = few;
     if (norm_in_gemm(g))
       g.row_norm = true;
     else if (!rinv_fused)
@@ -482,6 +491,7 @@ extern "C" adept_status adept_layer_step(const adept_layer_args* a, int layer, v
     go.A = a->attn_out; go.lda = dq; go.B = wo; go.ldb = dq; go.epi = EPI_RESID;
     go.C = a->h[out]; go.ldc = D; go.resid = a->h[in]; go.rows = act; go.name = "gemm_o";
     go.skinny_ws = ws.skinny; go.skinny_ws_bytes = ws.skinny_bytes;
+    go.few_rows = few;
     // 5. pre-FFN RMSNorm (gain folded into W_gate / W_up): its row factors
     //    come from the projection's epilogue on the skinny path
     if (dt == ADEPT_BF16 && gemm_skinny_row_norm(go)) {
@@ -496,6 +506,7 @@ extern "C" adept_status adept_layer_step(const adept_layer_args* a, int layer, v
     gu.epi = EPI_SWIGLU; gu.row_scale = ws.rinv;
     gu.C = a->ffn_act; gu.ldc = F; gu.name = "gemm_gate_up";
     gu.skinny_ws = ws.skinny; gu.skinny_ws_bytes = ws.skinny_bytes;
+    gu.few_rows = few;
     if (norm_in_gemm(gu))
       gu.row_norm = true;
     else if (!go.rinv_out)
@@ -507,6 +518,7 @@ extern "C" adept_status adept_layer_step(const adept_layer_args* a, int layer, v
     gd.A = a->ffn_act; gd.lda = F; gd.B = wd; gd.ldb = F; gd.epi = EPI_RESID;
     gd.C = a->h[out]; gd.ldc = D; gd.resid = a->h[out]; gd.rows = act; gd.name = "gemm_down";
     gd.skinny_ws = ws.skinny; gd.skinny_ws_bytes = ws.skinny_bytes;
+    gd.few_rows = few;
     ADEPT_TRY(exit_in_epilogue(gd));
     ADEPT_TRY(run_gemm(dt, gd, ws.gemm_tmp, s));
   }

@@ -97,3 +97,29 @@ def test_encoder_rows(seqs, length, stop):
                                           force_layer=force, on_layer=chk, stop_at_cls=stop)
     chk.finish(out, length)
     rep.summary()
+
+
+@pytest.mark.parametrize("seqs,direct", [(40, True), (48, False), (64, False)])
+def test_steps_are_of_one_kind(seqs, direct):
+    """Past 40 rows only the gate/up projection of this shape has too many weights for the
+    one-kernel form; then the others stay on the skinny path too, whose down projection
+    holds the exit test."""
+    import torch
+    shape = ai.DecoderShape(n_layers=2, d_model=512, n_heads=8, head_dim=64, d_ff=4096, vocab=320)
+    model = DecoderModel(shape, ai.decoder_weights(shape, seed=1, dtype="bf16"), dtype="bf16",
+                         rope_max_pos=64)
+    cache = model.new_cache(seqs, 3)
+    ids = torch.zeros(seqs, dtype=torch.int32, device="cuda")
+    B.timing_reset()
+    B.timing_enable(True)
+    model.decode_step(cache, ids, torch.zeros_like(ids), B.exit_cfg(0.9, shape.n_layers), pos_max=0)
+    torch.cuda.synchronize()
+    B.timing_enable(False)
+    names = sorted(B.timing_read())
+    say(f"rows={seqs}: {names}")
+    skinny = [n for n in names if "skinny" in n]
+    if direct:
+        assert not skinny and any("exit_compact" in n for n in names)
+    else:
+        assert any("ROW_EXIT" in n for n in skinny)
+        assert not any("exit_test" in n or "exit_compact" in n for n in names)
