@@ -307,8 +307,16 @@ __global__ void epilogue_f32_kernel(int epi, int M_max, const int32_t* M_dev, in
 }  // namespace
 
 // Rows and columns past the grid's 65535 y blocks, or leading dimensions that
-// break the 16-byte loads, take the general form.
+// break the 16-byte loads, take the general form, and so do outputs of many 64x64
+// tiles: a 16x16 block reads its operands four times as often as the general
+// form's tile, and once that has one or two workgroups per CU this decides.  The
+// two-block epilogues share the A block, so their line lies at twice the tiles.
+// Two layers, us, this kernel throughout / general form throughout / by this
+// rule: width 768, 512 rows 1637 / 2846 / 1644, 2048 rows 7772 / 5322 / 5316;
+// width 4096, 128 rows 6511 / 12622 / 6508, 1024 rows 51800 / 24122 / 24041.
 bool gemm_f32_fused(const GemmArgs& g) {
+  const bool two = g.epi == EPI_QKV || g.epi == EPI_SWIGLU;
+  if ((int64_t)ceil_div(g.M_max, FT) * ceil_div(g.N, FT) >= (two ? 512 : 256)) return false;
   const bool kind = g.epi == EPI_STORE || g.epi == EPI_RESID || g.epi == EPI_SWIGLU ||
                     (g.epi == EPI_QKV && g.head_dim % 32 == 0 && g.d_q % g.head_dim == 0);
   return kind && g.N > 0 && g.N <= 16 * 65535 && g.K > 0 && g.K % 4 == 0 && g.lda % 4 == 0 &&

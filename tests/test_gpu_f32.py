@@ -49,3 +49,32 @@ def test_f32_forms(shape, Bn, T):
     assert rel_err(st.logits.cpu().numpy(), st_o.logits) <= 1e-5
     k, v = (x.cpu().numpy().astype(np.float64) for x in (cache.k, cache.v))
     assert rel_err(k, cref.k) <= 1e-5 and rel_err(v, cref.v) <= 1e-5
+
+
+def test_f32_general_form_by_size():
+    """1280 rows: the outputs of many 64x64 tiles (QKV 780, O and down projections 260)
+    take the general form, gate/up (500) and the head stay on the other, and the norm's
+    factor reaches both; against the oracle at the f32 bound."""
+    shape = ai.DecoderShape(n_layers=2, d_model=832, n_heads=26, head_dim=32, d_ff=1600, vocab=100)
+    w = ai.decoder_weights(shape, seed=5, dtype="f32", std=0.03)
+    ids = ai.token_ids(5, shape.vocab, 10, 128)
+    force = (np.random.default_rng(5).random(ids.shape) < 0.3).astype(np.int32)
+    ref, cref = O.prefill(O.as64(w), shape, ids, O.ExitConfig(delta=math.inf), s_max=128,
+                          force_layer=force)
+    model = DecoderModel(shape, w, dtype="f32", rope_max_pos=128)
+    cache = model.new_cache(10, 128, fill=0.0)
+    B.timing_reset()
+    B.timing_enable(True)
+    res, _ = model.prefill(ids, B.exit_cfg(math.inf, shape.n_layers), s_max=128, force_layer=force,
+                           logits="all", cache=cache)
+    torch.cuda.synchronize()
+    B.timing_enable(False)
+    launches = {k: n for k, (n, _) in B.timing_read().items()}
+    general = sum(n for k, n in launches.items() if k.startswith("gemm_f32_kernel"))
+    fused = sum(n for k, n in launches.items() if "gemm_f32_mfma_kernel" in k)
+    print(launches, flush=True)
+    assert general == 3 * shape.n_layers   # QKV, O and down projections
+    assert fused == shape.n_layers + 2     # gate/up; the K/V generation, the head
+    assert rel_err(res.logits.cpu().numpy(), ref.logits) <= 1e-5
+    k, v = (x.cpu().numpy().astype(np.float64) for x in (cache.k, cache.v))
+    assert rel_err(k, cref.k) <= 1e-5 and rel_err(v, cref.v) <= 1e-5
