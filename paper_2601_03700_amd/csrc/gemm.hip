@@ -436,8 +436,8 @@ bool aligned8(const void* p) { return ((uintptr_t)p & 7u) == 0; }
 
 bool aligned_operands(const GemmArgs& g) {
   return aligned16(g.A) && aligned16(g.B) && (!g.B2 || aligned16(g.B2)) &&
-         (!g.a_sel || (g.A2 && aligned16(g.A2))) && g.lda % 8 == 0 &&
-         g.ldb % 8 == 0;
+         (!(g.a_sel || (g.list && g.list->exit_layer)) || (g.A2 && aligned16(g.A2))) &&
+         g.lda % 8 == 0 && g.ldb % 8 == 0;
 }
 
 }  // namespace

@@ -106,6 +106,26 @@ def test_host_validation_rejects_bad_arguments():
     _expect_invalid(L.adept_layer_step(ctypes.byref(a), 1, None))
 
 
+@pytest.mark.parametrize("seqs", [4, 16, 40, 64])
+def test_decode_step_checks_both_state_buffers(seqs):
+    """The fused schedule reads exited rows from the layer's output buffer: its alignment
+    is checked whichever GEMM form takes the list."""
+    a = B.LayerArgs()
+    for name, kind in B.LayerArgs._fields_:
+        if kind is ctypes.c_void_p:
+            setattr(a, name, 1 << 20)
+    a.dtype, a.n_layers, a.d_model, a.n_heads, a.head_dim, a.d_ff = B.BF16, 4, 256, 4, 64, 512
+    a.family, a.rms_eps, a.exit = 0, 1e-6, B.exit_cfg(0.9, 4)
+    a.n_tok = a.max_active = a.n_seq = a.n_slots = seqs
+    a.s_max = a.rope_max_pos = 1
+    a.kv_fused, a.attn_tiles, a.hsm = 1, 0, None
+    a.active[0], a.active[1], a.n_active[0], a.n_active[1] = (1 << 20, 1 << 21, 1 << 20, 1 << 21)
+    a.h[0], a.h[1] = 1 << 20, (1 << 21) + 2
+    a.workspace, a.workspace_bytes = 1 << 22, 1 << 40
+    _expect_invalid(B.lib().adept_layer_step(ctypes.byref(a), 1, None))
+    assert b"aligned" in B.lib().adept_last_error()
+
+
 def test_workspace_queries_are_host_only():
     assert B.compact_workspace_bytes(1000) == 0          # one workgroup
     assert B.compact_workspace_bytes(1 << 20) > 0        # multi-pass tiles
