@@ -345,7 +345,10 @@ extern "C" adept_status adept_encoder_layer_step(const adept_encoder_args* a, in
   // keys are one kernel, whose two words the first GEMM clears
   const bool direct = step_direct(a);
   const int few = direct ? kFewSplit : kFewSkinny;
-  const bool tail = direct && exit_compact_fits(a->exit, D, maxn, true);
+  const void* ln2_g = off(a->ln2_g, (int64_t)li * D);
+  const void* ln2_b = off(a->ln2_b, (int64_t)li * D);
+  const bool tail = direct && exit_compact_fits(a->exit, D, maxn, true) && aligned16(ln2_g) &&
+                    aligned16(ln2_b);   // else LN2 element by element (layernorm_rows)
   RowList list{};
   list.ticket = ws.ticket;
   if (tail) g.list = &list;
@@ -393,13 +396,11 @@ extern "C" adept_status adept_encoder_layer_step(const adept_encoder_args* a, in
     x.next = a->active[out]; x.n_next = a->n_active[out];
     x.exited = a->exited; x.n_exited = a->n_exited; x.exit_layer = a->exit_layer;
     x.ticket = ws.ticket;
-    x.ln_g = off(a->ln2_g, (int64_t)li * D); x.ln_b = off(a->ln2_b, (int64_t)li * D);
+    x.ln_g = ln2_g; x.ln_b = ln2_b;
     x.ln_eps = a->ln_eps; x.cls_seq_len = a->cls_stop ? a->seq_len : 0; x.key_live = a->key_live;
     return exit_compact(x, s);
   }
-  ADEPT_TRY(layernorm_rows(D, a->ln_eps, a->h[out], act, nact, maxn,
-                           off(a->ln2_g, (int64_t)li * D), off(a->ln2_b, (int64_t)li * D),
-                           a->h[out], s));
+  ADEPT_TRY(layernorm_rows(D, a->ln_eps, a->h[out], act, nact, maxn, ln2_g, ln2_b, a->h[out], s));
   // 6. exit test (Eq. 7-8), active-list update, exited keys leave the key set
   ADEPT_TRY(adept_exit_test(ADEPT_BF16, D, layer, &a->exit, act, nact, maxn, a->h[out], a->h[in],
                             a->inertia, a->force_layer, a->exit_flag, a->sim_out, stream));
