@@ -209,8 +209,8 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(GP p, RowList rl, i
       e.slot = p.slot ? p.slot[e.row] : e.row;
       if (rope) {
         const int64_t o = (int64_t)p.pos[e.row] * dn + (e.n & (dn - 1));
-        e.cs = *reinterpret_cast<const float4*>(p.rope_cos + o);
-        e.sn = *reinterpret_cast<const float4*>(p.rope_sin + o);
+        e.cs = rope4(p.rope_cos + o);
+        e.sn = rope4(p.rope_sin + o);
       }
     }
   }

@@ -203,6 +203,14 @@ __device__ __forceinline__ float4 bias4(const bf16* b, int64_t c) {
   return make_float4(bf2f(v[0]), bf2f(v[1]), bf2f(v[2]), bf2f(v[3]));
 }
 
+// Four values of a rotary table, which callers need not align past its floats
+// (passes above 64 rows read single ones): the unaligned load is one instruction.
+__device__ __forceinline__ float4 rope4(const float* t) {
+  typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+  const f32x4_any v = *reinterpret_cast<const f32x4_any*>(t);
+  return make_float4(v[0], v[1], v[2], v[3]);
+}
+
 __device__ __forceinline__ void dma16(const bf16* g, char* l) {
   __builtin_amdgcn_global_load_lds((glb_void_t*)g, (lds_void_t*)l, 16, 0, 0);
 }
@@ -983,8 +991,7 @@ __device__ __forceinline__ void epilogue4(const GP& p, int m, int n, float sc, f
       const float4 by = bias4(p.bias, n ^ half);
       const float y[4] = {y4.x * sc + by.x, y4.y * sc + by.y, y4.z * sc + by.z, y4.w * sc + by.w};
       const int64_t t = (int64_t)p.pos[row] * half + (c & (half - 1));
-      const float4 cs = *reinterpret_cast<const float4*>(p.rope_cos + t);
-      const float4 sn = *reinterpret_cast<const float4*>(p.rope_sin + t);
+      const float4 cs = rope4(p.rope_cos + t), sn = rope4(p.rope_sin + t);
       const float cv[4] = {cs.x, cs.y, cs.z, cs.w}, sv[4] = {sn.x, sn.y, sn.z, sn.w};
 #pragma unroll
       for (int e = 0; e < 4; ++e)

@@ -8,6 +8,7 @@ import sys
 
 import numpy as np
 import pytest
+import torch
 
 import adept_inputs as ai
 from oracle import adept_oracle as O
@@ -65,3 +66,25 @@ def test_encoder_rows(rows):
                                           force_layer=force, on_layer=chk)
     chk.finish(out, rows)
     rep.summary()
+
+
+@pytest.mark.parametrize("rows", [3, 30, 64, 65, 200])
+def test_rotary_tables_need_no_alignment(rows):
+    """Tables that start one float past a 16-byte boundary: the same bits."""
+    say(f"gemm tiles unaligned rotary tables rows={rows}")
+    shape = ai.DecoderShape(n_layers=1, d_model=1152, n_heads=9, head_dim=128, d_ff=384, vocab=128)
+    model = DecoderModel(shape, ai.decoder_weights(shape, seed=1, dtype="bf16"), dtype="bf16",
+                         rope_max_pos=512)
+    ids = ai.token_ids(rows, shape.vocab, 1, rows)
+    caches = []
+    for off in (0, 1):
+        if off:
+            for k in ("rope_cos", "rope_sin"):
+                t = getattr(model, k)
+                flat = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+                flat[1:] = t.flatten()
+                setattr(model, k, flat[1:].view(t.shape))
+        cache = model.new_cache(1, rows)
+        model.prefill(ids, B.exit_cfg(math.inf, 1), cache=cache)
+        caches.append(cache)
+    assert torch.equal(caches[0].k, caches[1].k) and torch.equal(caches[0].v, caches[1].v)
