@@ -86,7 +86,11 @@ adept_status launch_kv_x(GP p, int max_work, hipStream_t s) {
   p.tiles_n = ceil_div(p.N, GT::kTN);
   // one workgroup per tile: the host bound on them, rounded to whole XCD rounds
   const int flat = (max_work * (BM / GT::kTM) * p.tiles_n + 7) / 8 * 8;
-  ADEPT_LAUNCH((gemm_kv_flat_kernel<HD, EXT, GT>), dim3(flat), dim3(GT::kThreads), GT::kLds, s, p);
+  {
+    TimedLaunch tl(GT::kTN == 256 ? "gemm_kv_flat_kernel<256x256>" : "gemm_kv_flat_kernel<128x128>", s);
+    hipLaunchKernelGGL((gemm_kv_flat_kernel<HD, EXT, GT>), dim3(flat), dim3(GT::kThreads), GT::kLds,
+                       s, p);
+  }
   return launch_status("gemm_kv_grouped");
 }
 

@@ -47,6 +47,10 @@ __host__ __device__ inline MidPlan mid_plan(const MidTable& mt, int tiles_m, int
   return MidPlan{T - tail, tail, mt.S[tiles_m - 1]};
 }
 
+// Epilogues whose tiles are cut: the decoder layer's.  The encoder, the mapper
+// and the head give no workspace, and theirs stay whole.
+constexpr bool mid_cuts(int epi) { return epi != EPI_STORE && epi != EPI_GELU; }
+
 // Host: the plan table of a geometry (128 or 256 columns) for rows up to
 // M_max, and the bounds over it.  split == false: nothing is cut.
 struct MidBound {
@@ -103,7 +107,7 @@ __global__ __launch_bounds__(GT::kThreads, GT::kTN == 128 ? 2 : 1) void gemm_mid
     part = ws + ((int64_t)i * pl.S + s) * (kMidRows * GT::kTN);
   }
   raster_tile(t, tiles_m, p.tiles_n, &mt, &nt);
-  gemm_tile<EPI, false, HD, EXT, GT, true>(p, smem, 0, mt, nt, M, p.B, k0, k1 - k0, part);
+  gemm_tile<EPI, false, HD, EXT, GT, mid_cuts(EPI)>(p, smem, 0, mt, nt, M, p.B, k0, k1 - k0, part);
 }
 
 // Sum of the pieces of a cut tile of C columns at (row r, columns c..c+3);
@@ -151,6 +155,15 @@ __global__ __launch_bounds__(256) void mid_reduce_kernel(GP p, MidTable table,
                  [&]() { return mid_sum<C>(tile, pl.S, r, tc + 64); });
 }
 
+// The reduction's name in timings: epilogue and columns of a tile
+template <int EPI, int C> constexpr const char* mid_reduce_name() {
+  constexpr bool L = C == 256;
+  return EPI == EPI_QKV      ? (L ? "mid_reduce_qkv_256" : "mid_reduce_qkv_128")
+         : EPI == EPI_RESID  ? (L ? "mid_reduce_resid_256" : "mid_reduce_resid_128")
+         : EPI == EPI_SWIGLU ? (L ? "mid_reduce_swiglu_256" : "mid_reduce_swiglu_128")
+                             : (L ? "mid_reduce_gelu_tanh_256" : "mid_reduce_gelu_tanh_128");
+}
+
 template <int EPI, int HD, bool EXT, class GT>
 adept_status mid_launch_x(const GP& p, const char* name, float* ws, const MidTable& table,
                           const MidBound& b, hipStream_t s) {
@@ -163,10 +176,13 @@ adept_status mid_launch_x(const GP& p, const char* name, float* ws, const MidTab
                        GT::kLds, s, p, table, ws);
   }
   ADEPT_CHECK_LAUNCH("gemm_mid");
-  if (b.tail > 0) {
-    constexpr int kSlab = 1024 / (EPI == EPI_SWIGLU ? GT::kTN / 2 : GT::kTN);
-    ADEPT_LAUNCH((mid_reduce_kernel<EPI, GT::kTN>), dim3(kMidRows / kSlab, b.tail), dim3(256), 0, s,
-                 p, table, ws);
+  if constexpr (mid_cuts(EPI)) {
+    if (b.tail > 0) {
+      constexpr int kSlab = 1024 / (EPI == EPI_SWIGLU ? GT::kTN / 2 : GT::kTN);
+      TimedLaunch tl(mid_reduce_name<EPI, GT::kTN>(), s);
+      hipLaunchKernelGGL((mid_reduce_kernel<EPI, GT::kTN>), dim3(kMidRows / kSlab, b.tail),
+                         dim3(256), 0, s, p, table, ws);
+    }
     return launch_status("mid_reduce");
   }
   return ADEPT_OK;
@@ -186,7 +202,8 @@ adept_status gemm_mid(GP p, int epi, const char* name, float* ws, size_t ws_byte
   p.tiles_n = mid_tiles_n(C, p.N, epi);
   const int KT = p.K / BK;
   MidTable t{};
-  const bool split = ws_bytes > 0 && ws_bytes >= mid_ws_bytes(p.M_max, p.N, p.K, epi);
+  const bool split = mid_cuts(epi) && ws_bytes > 0 &&
+                     ws_bytes >= mid_ws_bytes(p.M_max, p.N, p.K, epi);
   MidBound b = mid_table(C, p.M_max, p.tiles_n, KT, split, &t);
   if ((size_t)b.pieces * kMidRows * C * sizeof(float) > ws_bytes)
     b = mid_table(C, p.M_max, p.tiles_n, KT, false, &t);

@@ -94,7 +94,7 @@ MidBound mid_table(int cols, int M_max, int tiles_n, int KT, bool split, MidTabl
 // An upper bound over the plans (no plan is made): a round's pieces of either
 // tile are 32 MiB, and there are no more than every tile cut kMidMaxS ways.
 size_t mid_ws_bytes(int M_max, int N, int K, int epi) {
-  if (M_max <= 0 || N <= 0 || K < BK) return 0;
+  if (!mid_cuts(epi) || M_max <= 0 || N <= 0 || K < BK) return 0;
   const int64_t most = std::min(K / BK / kMidMinStages, kMidMaxS);
   if (most < 2) return 0;
   // in 128x128 tiles, of which a 128x256 tile is two
@@ -110,7 +110,8 @@ MidTile mid_choose(const GP& p, int epi, size_t ws_bytes) {
   const bool gelu = epi == EPI_GELU || epi == EPI_GELU_TANH;
   double best = ceil_div(tl, 256) * (kLargeFixed + (gelu ? kLargeGelu : 0.0) + kLargeStage * KT);
   MidTile pick = kTileLarge;
-  const bool split = ws_bytes > 0 && ws_bytes >= mid_ws_bytes(p.M_max, p.N, p.K, epi);
+  const bool split = mid_cuts(epi) && ws_bytes > 0 &&
+                     ws_bytes >= mid_ws_bytes(p.M_max, p.N, p.K, epi);
   const double b = best_plan(kTileB, tm, mid_tiles_n(256, p.N, epi), KT, split, &tail, &S);
   if (b < best) { best = b; pick = kTile128x256; }
   const double a = best_plan(kTileA, tm, mid_tiles_n(128, p.N, epi), KT, split, &tail, &S);
