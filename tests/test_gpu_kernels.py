@@ -327,9 +327,10 @@ def _check_kv(dt, shape, s, wkv, gain, el, rows, pos, slot, n_slots, kc, vc):
 
 @pytest.mark.parametrize("D", [64, 128, 192, 320, 448, 512, 576, 704, 1024])
 def test_kv_generate_k_depths(D):
-    """The GEMM K loop at 1..16 stages of 64: fewer stages than the
-    five-slot ring, every remainder of KT mod 5 before the groups of five,
-    and the clamped loads past the last stage."""
+    """The GEMM K loop at 1..16 stages of 64 (128x128 tiles; the 256x256 ones:
+    test_gpu_kv_tiles.py): fewer stages than the five-slot ring, every
+    remainder of KT mod 5 before the groups of five, and the clamped loads
+    past the last stage."""
     say(f"kv_generate K depth D={D}")
     dt, N, H, hd, n_tok = "bf16", 3, 2, 128, 300
     shape, s, wkv, gain, el = _kv_case(dt, N, D, H, hd, n_tok, 500 + D, std=D ** -0.5)

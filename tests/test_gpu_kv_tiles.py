@@ -1,7 +1,10 @@
 """The two tile sizes of the grouped K/V generation: few tiles (128x128) and
-more (256x256), rows at the edges of either, an empty second half of a 256-row
-item, ragged columns.  Against plain torch in 64 bits; one bf16 rounding of
-sums with f32 error, per element."""
+more than 512 of 256x256, rows at the edges of either, an empty second half of a
+256-row item, ragged columns, K of few stages.  Which tile ran is read from the
+kernels' names.  Against plain torch in 64 bits; one bf16 rounding of sums with
+f32 error, per element."""
+import contextlib
+
 import numpy as np
 import pytest
 import torch
@@ -17,6 +20,18 @@ def _normal(dims, seed, std=1.0):
     return (torch.randn(dims, generator=g, device=DEV) * std).to(torch.bfloat16)
 
 
+@contextlib.contextmanager
+def _on_tiles(name):
+    """The K/V generation inside runs on these tiles."""
+    B.timing_reset()
+    B.timing_enable(True)
+    yield
+    torch.cuda.synchronize()
+    B.timing_enable(False)
+    ran = [n for n in B.timing_read() if "gemm_kv_flat" in n]
+    assert ran == [f"gemm_kv_flat_kernel<{name}>"], ran
+
+
 def _close(got, want, K):
     # the result's bf16 rounding (up to 2^-8 of it) and f32 sums of K products
     # (about K 2^-24 of the result's spread)
@@ -27,7 +42,21 @@ def _close(got, want, K):
 @pytest.mark.parametrize("layers,rows", [(2, 1), (2, 127), (2, 128), (3, 129), (3, 256), (4, 257),
                                          (40, 385)])
 def test_rmsnorm_family(layers, rows):
-    D, H, hd = 320, 4, 64
+    with _on_tiles("128x128"):
+        _rmsnorm(layers, rows, 320, 4, 64)
+
+
+# K of 1 to 7 stages: fewer than the five slots of the ring, each remainder past them
+@pytest.mark.parametrize("D,rows,hd", [(64, 1025, 64), (128, 1056, 128), (192, 1280, 64),
+                                       (256, 1281, 128), (320, 1025, 128), (384, 1100, 64),
+                                       (448, 1152, 128)])
+def test_rmsnorm_family_many_tiles(D, rows, hd):
+    with _on_tiles("256x256"):
+        _rmsnorm(64, rows, D, 256 // hd, hd)     # 640 tiles at least
+
+
+def _rmsnorm(layers, rows, D, H, hd):
+    print(f"kv tiles layers={layers} rows={rows} D={D} hd={hd}", flush=True)
     s, w = _normal((rows, D), rows), _normal((layers, 2 * H * hd, D), layers, 0.05)
     el = torch.from_numpy(np.random.default_rng(rows).integers(1, layers + 1, rows).astype(np.int32)).to(DEV)
     idx = torch.arange(rows, dtype=torch.int32, device=DEV)
@@ -53,7 +82,19 @@ def test_rmsnorm_family(layers, rows):
 
 @pytest.mark.parametrize("layers,rows", [(2, 128), (3, 200), (3, 257), (40, 300)])
 def test_layernorm_family(layers, rows):
-    D, H, hd = 448, 5, 64               # 640 columns: ragged 256-column tiles
+    with _on_tiles("128x128"):
+        _layernorm(layers, rows, 448)
+
+
+@pytest.mark.parametrize("D,rows", [(64, 769), (192, 800), (448, 1024)])
+def test_layernorm_family_many_tiles(D, rows):
+    with _on_tiles("256x256"):
+        _layernorm(64, rows, D)
+
+
+def _layernorm(layers, rows, D):
+    H, hd = 5, 64                       # 640 columns: ragged 256-column tiles
+    print(f"kv tiles layernorm layers={layers} rows={rows} D={D}", flush=True)
     s, w = _normal((rows, D), rows), _normal((layers, 2 * H * hd, D), layers, 0.05)
     bias = _normal((layers, 2 * H * hd), 7, 0.1)
     el = torch.from_numpy(np.random.default_rng(rows).integers(1, layers + 1, rows).astype(np.int32)).to(DEV)
