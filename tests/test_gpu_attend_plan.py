@@ -19,6 +19,20 @@ DEV = "cuda"
                                                     (4, 1024, 1.0, ()), (5, 1024, 0.79, (4,)),
                                                     (4, 1040, 1.0, (1,)), (9, 520, 0.95, (0, 8))])
 def test_tiles(n_seq, length, keep, gone):
+    _tiles(n_seq, length, keep, gone, False)
+
+
+# more than 4096 entries: the first or the last sequence gone, one entry past the
+# line, sequences that end on a tile, more sequences than a wave has lanes
+@pytest.mark.parametrize("n_seq,length,keep,gone", [(1, 4097, 1.0, ()), (5, 1025, 1.0, (0,)),
+                                                    (9, 640, 1.0, (0, 8)), (6, 1024, 0.9, (5,)),
+                                                    (130, 40, 0.95, (0, 64, 129))])
+def test_tiles_of_long_lists(n_seq, length, keep, gone):
+    _tiles(n_seq, length, keep, gone, True)
+
+
+def _tiles(n_seq, length, keep, gone, searched):
+    print(f"attention plan {n_seq}x{length} keep={keep} gone={gone}", flush=True)
     H, hd = 2, 64
     rng = np.random.default_rng(n_seq * length)
     n_tok = n_seq * length
@@ -29,6 +43,7 @@ def test_tiles(n_seq, length, keep, gone):
     live[n_tok // 2] = True
     act = np.flatnonzero(live).astype(np.int32)
     n = act.size
+    assert (n > 4096) == searched   # the plan's line between scan and search
     i32 = dict(dtype=torch.int32, device=DEV)
     pos = torch.arange(length, **i32).repeat(n_seq)
     seq = torch.arange(n_seq, **i32).repeat_interleave(length)
