@@ -53,7 +53,7 @@ def _tf_classify(model, w, ids, delta, metric="global", force=None, stop_at_cls=
 
 
 @pytest.mark.parametrize("stop_at_cls", [True, False])
-@pytest.mark.parametrize("Bn,T", [(3, 100), (2, 24)])   # tiled GEMMs; skinny GEMMs (48 rows)
+@pytest.mark.parametrize("Bn,T", [(3, 100), (2, 24)])   # tiled GEMMs; one kernel each (48 rows)
 def test_classify_forced_schedule(enc, Bn, T, stop_at_cls):
     w32, w, model = enc
     say(f"classify forced schedule B={Bn} T={T} stop_at_cls={stop_at_cls}")

@@ -30,6 +30,13 @@ RAGGED = ai.EncoderShape(n_layers=3, d_model=832, n_heads=13, head_dim=64, d_ff=
                          max_pos=512)
 
 
+# LayerNorm rows of two and four chunks per thread in the exit kernel
+CHUNKS2 = ai.EncoderShape(n_layers=2, d_model=1152, n_heads=18, head_dim=64, d_ff=1152, vocab=50,
+                          max_pos=512)
+CHUNKS4 = ai.EncoderShape(n_layers=2, d_model=2176, n_heads=34, head_dim=64, d_ff=640, vocab=50,
+                          max_pos=512)
+
+
 def _final(model, shape, ids, force):
     """(logits, final state of every row, exit layers) of one call."""
     r = model.classify(ids, B.exit_cfg(math.inf, shape.n_layers), force_layer=force)
@@ -63,7 +70,8 @@ def test_more_than_64_rows(length, counts):
 
 @pytest.mark.parametrize("shape,length,counts", [(LARGE, 12, (1, 2, 3, 5)), (LARGE, 20, (1, 2, 3)),
                                                  (RAGGED, 12, (1, 2, 3, 5)), (RAGGED, 20, (1, 2, 3)),
-                                                 (RAGGED, 1, (1, 16, 17, 64))])
+                                                 (RAGGED, 1, (1, 16, 17, 64)),
+                                                 (CHUNKS2, 12, (1, 2, 5)), (CHUNKS4, 12, (1, 2))])
 def test_up_to_64_rows(shape, length, counts):
     _same_alone_and_beside(shape, length, counts)
 

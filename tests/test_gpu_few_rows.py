@@ -21,10 +21,22 @@ pytestmark = pytest.mark.gpu
 # K of 4, 9, 13 and 26 pieces; heads of 64 and 128
 LLAMA = ai.DecoderShape(n_layers=3, d_model=832, n_heads=6, head_dim=128, d_ff=1664, vocab=384)
 SMALL = ai.DecoderShape(n_layers=3, d_model=256, n_heads=4, head_dim=64, d_ff=640, vocab=320)
-# past the narrow-layer rule of 17 and more rows (down projection), wide blocks
+# up to 16 rows only (gate/up and down projections of more weights than the rule allows)
 WIDE = ai.DecoderShape(n_layers=3, d_model=2048, n_heads=16, head_dim=128, d_ff=6272, vocab=256)
 GPT2 = ai.DecoderShape(n_layers=3, d_model=576, n_heads=9, head_dim=64, d_ff=1664, vocab=448,
                        family="gpt2", max_pos=512)
+# 32 weight rows per workgroup (4096 columns and more) at 17 to 40 rows: rotary QKV,
+# SwiGLU and the head; QKV and tanh GELU of the LayerNorm family
+BLOCK32 = ai.DecoderShape(n_layers=3, d_model=1472, n_heads=12, head_dim=128, d_ff=2432, vocab=4160)
+BLOCK32_64 = ai.DecoderShape(n_layers=2, d_model=1472, n_heads=24, head_dim=64, d_ff=2432, vocab=4160)
+XL = ai.DecoderShape(n_layers=2, d_model=1600, n_heads=25, head_dim=64, d_ff=6400, vocab=4160,
+                     family="gpt2", max_pos=512)
+# rows of 2304 and 4352: three and five elements' chunks per thread in the exit test
+ROW4 = ai.DecoderShape(n_layers=3, d_model=2304, n_heads=18, head_dim=128, d_ff=256, vocab=128)
+ROW8 = ai.DecoderShape(n_layers=2, d_model=4352, n_heads=34, head_dim=128, d_ff=256, vocab=128)
+# the erf GELU of both forms: up to 40 rows one kernel, then the skinny path
+ENC_WIDE = ai.EncoderShape(n_layers=3, d_model=1024, n_heads=16, head_dim=64, d_ff=4096, vocab=500,
+                           max_pos=512)
 ENC = ai.EncoderShape(n_layers=3, d_model=768, n_heads=12, head_dim=64, d_ff=1600, vocab=500,
                       max_pos=512)
 
@@ -81,10 +93,33 @@ def test_decode_rows(shape, seqs, kv_fused):
     _run(shape, seqs, 3, kv_fused, decode=True)
 
 
+@pytest.mark.parametrize("shape,rows", [(BLOCK32, 24), (BLOCK32, 40), (BLOCK32_64, 33), (XL, 24),
+                                        (XL, 40), (XL, 48), (ROW4, 9), (ROW8, 3)])
+def test_prefill_wide_rows(shape, rows):
+    say(f"few rows, prefill {shape.family} width={shape.d_model} rows={rows}")
+    _run(shape, 1, rows)
+
+
+@pytest.mark.parametrize("shape,seqs", [(BLOCK32, 20), (BLOCK32, 37), (BLOCK32_64, 24), (XL, 24),
+                                        (XL, 40), (ROW4, 16)])
+def test_decode_wide_rows(shape, seqs):
+    say(f"few rows, decode {shape.family} width={shape.d_model} seqs={seqs}")
+    _run(shape, seqs, 1, decode=True)
+
+
+@pytest.mark.parametrize("seqs,length", [(1, 20), (2, 20), (3, 20)])
+def test_encoder_wide_rows(seqs, length):
+    _encoder(ENC_WIDE, seqs, length, True)
+
+
 @pytest.mark.parametrize("seqs,length", [(1, 1), (1, 17), (4, 16), (3, 11), (16, 4)])
 @pytest.mark.parametrize("stop", [True, False])
 def test_encoder_rows(seqs, length, stop):
-    say(f"few rows, encoder {seqs}x{length} stop={stop}")
+    _encoder(ENC, seqs, length, stop)
+
+
+def _encoder(ENC, seqs, length, stop):
+    say(f"few rows, encoder width={ENC.d_model} {seqs}x{length} stop={stop}")
     rows = seqs * length
     w32 = ai.encoder_weights(ENC, seed=rows, dtype="bf16")
     ids = ai.token_ids(rows, ENC.vocab, seqs, length)
