@@ -35,6 +35,11 @@ CHUNKS2 = ai.EncoderShape(n_layers=2, d_model=1152, n_heads=18, head_dim=64, d_f
                           max_pos=512)
 CHUNKS4 = ai.EncoderShape(n_layers=2, d_model=2176, n_heads=34, head_dim=64, d_ff=640, vocab=50,
                           max_pos=512)
+# 32 weight rows per workgroup in QKV; in the projections back to the width
+QKV32 = ai.EncoderShape(n_layers=2, d_model=1472, n_heads=23, head_dim=64, d_ff=1472, vocab=50,
+                        max_pos=512)
+BACK32 = ai.EncoderShape(n_layers=2, d_model=4096, n_heads=16, head_dim=64, d_ff=640, vocab=50,
+                         max_pos=512)
 
 
 def _final(model, shape, ids, force):
@@ -71,7 +76,8 @@ def test_more_than_64_rows(length, counts):
 @pytest.mark.parametrize("shape,length,counts", [(LARGE, 12, (1, 2, 3, 5)), (LARGE, 20, (1, 2, 3)),
                                                  (RAGGED, 12, (1, 2, 3, 5)), (RAGGED, 20, (1, 2, 3)),
                                                  (RAGGED, 1, (1, 16, 17, 64)),
-                                                 (CHUNKS2, 12, (1, 2, 5)), (CHUNKS4, 12, (1, 2))])
+                                                 (CHUNKS2, 12, (1, 2, 5)), (CHUNKS4, 12, (1, 2)),
+                                                 (QKV32, 20, (1, 2, 3)), (BACK32, 20, (1, 2, 3))])
 def test_up_to_64_rows(shape, length, counts):
     _same_alone_and_beside(shape, length, counts)
 

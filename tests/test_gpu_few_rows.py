@@ -31,6 +31,7 @@ BLOCK32 = ai.DecoderShape(n_layers=3, d_model=1472, n_heads=12, head_dim=128, d_
 BLOCK32_64 = ai.DecoderShape(n_layers=2, d_model=1472, n_heads=24, head_dim=64, d_ff=2432, vocab=4160)
 XL = ai.DecoderShape(n_layers=2, d_model=1600, n_heads=25, head_dim=64, d_ff=6400, vocab=4160,
                      family="gpt2", max_pos=512)
+BACK32 = ai.DecoderShape(n_layers=2, d_model=4096, n_heads=8, head_dim=128, d_ff=1536, vocab=128)
 # rows of 2304 and 4352: three and five elements' chunks per thread in the exit test
 ROW4 = ai.DecoderShape(n_layers=3, d_model=2304, n_heads=18, head_dim=128, d_ff=256, vocab=128)
 ROW8 = ai.DecoderShape(n_layers=2, d_model=4352, n_heads=34, head_dim=128, d_ff=256, vocab=128)
@@ -94,7 +95,8 @@ def test_decode_rows(shape, seqs, kv_fused):
 
 
 @pytest.mark.parametrize("shape,rows", [(BLOCK32, 24), (BLOCK32, 40), (BLOCK32_64, 33), (XL, 24),
-                                        (XL, 40), (XL, 48), (ROW4, 9), (ROW8, 3)])
+                                        (XL, 40), (XL, 48), (BACK32, 24), (BACK32, 40), (ROW4, 9),
+                                        (ROW8, 3)])
 def test_prefill_wide_rows(shape, rows):
     say(f"few rows, prefill {shape.family} width={shape.d_model} rows={rows}")
     _run(shape, 1, rows)

@@ -83,6 +83,13 @@ def test_hsm_forward_matches_oracle(D, n_tok, n_rows, updated):
     np.testing.assert_array_equal(got2[others], h[others])
 
 
+# the one-kernel GEMMs of few rows: blocks of 16, 32 and 64 rows; 16 weight rows per
+# workgroup and (D = 512: 4096 columns of fc2) 32
+@pytest.mark.parametrize("D,n_rows", [(256, 9), (256, 20), (256, 50), (512, 15), (512, 30)])
+def test_hsm_few_rows(D, n_rows):
+    test_hsm_forward_matches_oracle(D, 100, n_rows, 1)
+
+
 def test_hsm_forward_empty_and_errors():
     say("hsm empty / errors")
     D = 256
