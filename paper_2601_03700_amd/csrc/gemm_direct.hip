@@ -359,7 +359,7 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(GP p, RowList rl, i
     }
     const float4 x4 = sum(y * NB + x, lane);
     const float bx[4] = {bf2f(e.bias[0]), bf2f(e.bias[1]), bf2f(e.bias[2]), bf2f(e.bias[3])};
-    const float v[4] = {x4.x * sc + bx[0], x4.y * sc + bx[1], x4.z * sc + bx[2], x4.w * sc + bx[3]};
+    float v[4] = {x4.x * sc + bx[0], x4.y * sc + bx[1], x4.z * sc + bx[2], x4.w * sc + bx[3]};
     bf16x4_t o;
     if constexpr (EPI == EPI_STORE) {
       if (p.c_f32) {
@@ -393,10 +393,10 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(GP p, RowList rl, i
         for (int c = 0; c < 4; ++c) o[c] = f2bf(v[c]);
       }
     } else {
+      if constexpr (EPI == EPI_GELU) gelu_erf(v);
 #pragma unroll
       for (int c = 0; c < 4; ++c)
-        o[c] = f2bf(EPI == EPI_GELU        ? gelu_erf(v[c])
-                    : EPI == EPI_GELU_TANH ? gelu_tanh(v[c])
+        o[c] = f2bf(EPI == EPI_GELU_TANH   ? gelu_tanh(v[c])
                     : EPI == EPI_RESID     ? v[c] + bf2f(e.resid[c])
                                            : v[c]);
     }

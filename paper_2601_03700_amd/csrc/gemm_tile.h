@@ -168,7 +168,7 @@ __device__ __forceinline__ float silu(float g) {
 // (6e-4 of the values in (-1, 0), 3e-3 in (-2, -1), 4e-2 in (-3, -2)).  The two-branch erff took 110 of the
 // 270 us of a 32768 x 3072 GELU projection.
 constexpr float kGeluErr = 4.5e-7f;   // the largest over all floats: 2.98e-7
-__device__ __forceinline__ float gelu_erf(float x) {
+__device__ __forceinline__ uint32_t gelu_ends(float x) {   // low and high end, rounded
   const float a = fabsf(x);
   const float t = __builtin_amdgcn_rcpf(fmaf(0.2121320366859436f, a, 1.0f));
   float q = -0.06472896039485931f;
@@ -182,11 +182,24 @@ __device__ __forceinline__ float gelu_erf(float x) {
   q = fmaf(q, t, 0.08459459245204926f);
   const float h = t * q * __expf(-0.5f * a * a);   // Phi(-a)
   const float y = x * (x < 0.0f ? h : 1.0f - h), e = kGeluErr * a;
-  const uint32_t w = pack_bf16x2(y - e, y + e);
-  float r = __uint_as_float(w << 16);
-  if ((w ^ (w << 16)) >> 16)   // NaN too
-    r = bf2f(f2bf(0.5f * x * (1.0f + erff(x * 0.7071067811865476f))));
-  return r;
+  return pack_bf16x2(y - e, y + e);
+}
+// N values in place; the few that need erff are one branch for all of them
+template <int N> __device__ __forceinline__ void gelu_erf(float (&x)[N]) {
+  uint32_t w[N], open = 0;
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
+    w[n] = gelu_ends(x[n]);
+    open |= (w[n] ^ (w[n] << 16)) >> 16;   // the ends differ (or NaN and not)
+  }
+  if (open) {
+#pragma unroll
+    for (int n = 0; n < N; ++n)
+      if ((w[n] ^ (w[n] << 16)) >> 16)
+        w[n] = f2bf(0.5f * x[n] * (1.0f + erff(x[n] * 0.7071067811865476f)));
+  }
+#pragma unroll
+  for (int n = 0; n < N; ++n) x[n] = __uint_as_float(w[n] << 16);
 }
 
 // x * Phi(x) with the tanh approximation of the normal CDF (GPT-2's MLP):
@@ -764,9 +777,9 @@ __device__ __forceinline__ void gemm_tile(const GP& p, char* smem, int layer, in
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
             x[e] = f[e] * scv[q] + bv[e];
-            if constexpr (EPI == EPI_GELU) x[e] = gelu_erf(x[e]);
             if constexpr (EPI == EPI_GELU_TANH) x[e] = gelu_tanh(x[e]);
           }
+          if constexpr (EPI == EPI_GELU) gelu_erf(x);
           if constexpr (EPI == EPI_RESID) {
             const uint32_t rw[4] = {rres[q].x, rres[q].y, rres[q].z, rres[q].w};
 #pragma unroll
@@ -864,10 +877,9 @@ __device__ __forceinline__ void gemm_tile(const GP& p, char* smem, int layer, in
             const float x[4] = {x4[r].x * sc[r] + bx.x, x4[r].y * sc[r] + bx.y,
                                 x4[r].z * sc[r] + bx.z, x4[r].w * sc[r] + bx.w};
             bf16x4_t o;
-            if (EPI == EPI_GELU || EPI == EPI_GELU_TANH) {
+            if (EPI == EPI_GELU_TANH) {
 #pragma unroll
-              for (int e = 0; e < 4; ++e)
-                o[e] = f2bf(EPI == EPI_GELU ? gelu_erf(x[e]) : gelu_tanh(x[e]));
+              for (int e = 0; e < 4; ++e) o[e] = f2bf(gelu_tanh(x[e]));
               if ((!kCheck || m < M) && col_in)
                 *reinterpret_cast<bf16x4_t*>(reinterpret_cast<bf16*>(p.C) + (int64_t)m * p.ldc +
                                              nw + c4) = o;
@@ -945,11 +957,12 @@ template <int EPI, class Partner, class Up>
 __device__ __forceinline__ void epilogue4(const GP& p, int m, int n, float sc, float4 x4,
                                           Partner&& partner, Up&& up) {
   const float4 bx = bias4(p.bias, n);
-  const float x[4] = {x4.x * sc + bx.x, x4.y * sc + bx.y, x4.z * sc + bx.z, x4.w * sc + bx.w};
+  float x[4] = {x4.x * sc + bx.x, x4.y * sc + bx.y, x4.z * sc + bx.z, x4.w * sc + bx.w};
   bf16x4_t o;
   if (EPI == EPI_GELU || EPI == EPI_GELU_TANH) {
+    if constexpr (EPI == EPI_GELU) gelu_erf(x);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) o[e] = f2bf(EPI == EPI_GELU ? gelu_erf(x[e]) : gelu_tanh(x[e]));
+    for (int e = 0; e < 4; ++e) o[e] = f2bf(EPI == EPI_GELU ? x[e] : gelu_tanh(x[e]));
     *reinterpret_cast<bf16x4_t*>(reinterpret_cast<bf16*>(p.C) + (int64_t)m * p.ldc + n) = o;
   } else if (EPI == EPI_STORE) {
     const int64_t off = (int64_t)m * p.ldc + n;
