@@ -414,17 +414,14 @@ adept_status kvgen_f32_fused(const GemmArgs& g, int n_layers, const int32_t* exi
 adept_status gemm_f32_direct(const GemmArgs& g, hipStream_t s);           // f32, C = A B^T
 // adept_kv_generate / adept_kv_generate_layernorm (csrc/kvgen.hip) of rows that
 // skip at most max_skipped layers
-adept_status kv_generate_upto(int max_skipped, adept_dtype dt, int n_layers, int d_model, int n_heads,
-                                     int head_dim, float eps, const void* s_map,
-                                     const int32_t* rows, const int32_t* n_rows,
-                                     int max_rows, const int32_t* exit_layer,
-                                     const int32_t* cache_slot, const int32_t* pos,
-                                     const void* w_kv, int64_t w_kv_layer_stride,
-                                     const void* attn_gain, const float* rope_cos,
-                                     const float* rope_sin, int rope_max_pos,
-                                     void* k_cache, void* v_cache, int64_t n_slots,
-                                     void* workspace, size_t workspace_bytes,
-                                     void* stream);
+adept_status kv_generate_upto(int max_skipped, adept_dtype dt, int n_layers, int d_model,
+                              int n_heads, int head_dim, float eps, const void* s_map,
+                              const int32_t* rows, const int32_t* n_rows, int max_rows,
+                              const int32_t* exit_layer, const int32_t* cache_slot,
+                              const int32_t* pos, const void* w_kv, int64_t w_kv_layer_stride,
+                              const void* attn_gain, const float* rope_cos, const float* rope_sin,
+                              int rope_max_pos, void* k_cache, void* v_cache, int64_t n_slots,
+                              void* workspace, size_t workspace_bytes, void* stream);
 adept_status kv_generate_layernorm_upto(
     int max_skipped, adept_dtype dt, int n_layers, int d_model, int n_heads, int head_dim, float eps,
     const void* s_map, const int32_t* rows, const int32_t* n_rows, int max_rows,

@@ -78,7 +78,7 @@ __global__ __launch_bounds__(256) void encoder_embed_kernel(
 // l, l+64, ...; d a multiple of 8 up to 512 R): every table row is read once, by
 // 16-byte loads.  The sums are those of the kernel above, in which lane l adds up
 // the elements l, l+64, ...: the row passes through LDS for them.  32768 rows of
-// 768: 70 us element by element over three passes, 24 so.
+// 768: 70 us element by element over three passes, 33 so.
 template <int R>
 __global__ __launch_bounds__(256) void encoder_embed_vec_kernel(
     int n, int d, int vocab, int max_pos, float eps, const int32_t* __restrict__ ids,
@@ -227,8 +227,8 @@ EncWs carve(const adept_encoder_args* a, void* base) {
   // chain of sums over K, whichever tile forms it, so a sequence's states do not
   // depend on how many rows run beside it.  Two class logits after twelve layers
   // of bf16 rounding follow every change of order (by up to 5 % with cut tiles).
-  // Without the cuts twelve layers of width 768 take 1175 us at 100 rows (956 with
-  // them, 2159 on 256x256 tiles), 1415 at 2000 (1294, 2565).
+  // Without the cuts twelve layers of width 768 take 1157 us at 100 rows (961 with
+  // them, 2150 on 256x256 tiles), 1384 at 2000 (1276, 2562).
   if (w.parts_bytes) {
     w.parts = (float*)(p + off);
     off += align256(w.parts_bytes);

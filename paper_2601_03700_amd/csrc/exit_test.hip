@@ -204,7 +204,7 @@ adept_status launch_exit(int ch, const ExitParams& p, int max_active, const int3
 // Separate kernels are a launch, a row count and a list read each: at 24 rows
 // of 1600 the exit test took 12.7 us in the down projection's epilogue and the
 // compaction 4.0; together 4.3.  An encoder layer's five (48 rows of 768):
-// LayerNorm 4.0, exit test 4.2, early stop 1.8, compaction 4.2, dead keys 1.5;
+// LayerNorm 4.0, exit test 4.2, early stop 1.8, compaction 4.2, dead keys 1.4;
 // together 7.9.
 struct SmallExit {
   const int32_t* rows;

@@ -1,9 +1,9 @@
 // Dense and grouped GEMMs of the hot path, C[m][n] = sum_k A[m][k] B[n][k]
 // (B in nn.Linear [out][in] order, so both operands are K-contiguous).
 //
-// bf16 path: gemm_tile.h's 256x256 tile when the rows are many; 128x128 tiles
-// in gemm_mid.hip otherwise; the skinny path below for 17 to 64 rows of wide
-// layers, gemm_direct.hip for the rest of them.
+// bf16 path: gemm_tile.h's 256x256 tile when the rows are many; the 128x256 and
+// 128x128 tiles of gemm_mid.h otherwise; the skinny path below for 17 to 64 rows
+// of wide layers, gemm_direct.hip for the rest of them.
 //
 // Workgroups are mapped to tiles XCD by XCD: the hardware deals consecutive
 // workgroup ids round-robin to the 8 XCDs, so the id is remapped to give each

@@ -19,8 +19,8 @@
 // by kernels of their own.  Measured, us, GEMM and epilogue kernel of the
 // split form -> this one: 7B width, 1 row, a layer's four GEMMs with their
 // norms and row list 131 -> 102 (4.5 TB/s of weights in gate/up); width 1600,
-// 24 rows, QKV / first MLP 13.5 / 13.0 -> 11.0 / 10.3; width 768, 48 rows, QKV
-// 10.2 -> 6.6.
+// 24 rows, QKV / first MLP 13.5 / 13.0 -> 11.0 / 10.3; width 768, 48 rows, biased
+// QKV 9.4 -> 6.8, in the skinny path's order (SPLIT) 8.0.
 #include "gemm_tile.h"
 
 namespace adept {
@@ -467,8 +467,13 @@ adept_status dir_rows(const GP& p, const RowList& rl, int row_norm, const char* 
 // the CUs binds: at the 7B widths and 64 rows 35 to 73 us a GEMM, 16 to 43 for
 // the skinny path's two kernels; at width 1600 (10 M weights) a decode step of
 // 24 rows 4000 us against 4530, of 40 4471 against 4661, of 48 the same, of 64
-// 5412 against 5141 (5246 with only the O projection, 2.6 M, on it); at width
-// 768 (2.4 M) and 64 rows 713 against 789.
+// 5412 against 5141; two layers of width 1600, 40 / 48 / 64 rows 152 / 162 / 185
+// against 156 / 153 / 160.  Past 40 rows the line lies below the least width that
+// lost (LayerNorm family, width 1024, 4.2 M: 48 / 64 rows 122 / 137 against 124 /
+// 128), at the widest that was measured to win (width 768, 2.36 M: 108 / 118
+// against 118 / 121); steps of the RMSNorm family would win up to 5.8 M (width 1024,
+// 48 rows 103 against 127).  A step takes the form for all its GEMMs or none
+// (layer.hip, encoder.hip).
 // Plain stores (the head) of wide layers stream better through the tiles of
 // gemm_mid.h (6 rows, 32000 x 4096: 52 us, 58 here).
 bool gemm_direct_fits(int M_max, int n_weights, int K, int epi) {

@@ -3,8 +3,8 @@
 //
 // Main form: one workgroup per 16 x 16 outputs (QKV and SwiGLU: per 16 x 2 x 16,
 // a block of columns and its rotary partner, or gate and up), its four or
-// sixteen waves taking every fourth or sixteenth 32-deep piece of K; the waves' sums meet in LDS, in
-// wave order, where the epilogue runs, with the row's RMSNorm factor formed
+// sixteen waves taking every fourth or sixteenth 32-deep piece of K; the waves'
+// sums meet in LDS, in wave order, where the epilogue runs, with the row's RMSNorm factor formed
 // from the A values on the way when asked.  The shapes are small (128 x 256,
 // K = 1024): what bounds them is the chip they leave idle and the chain of
 // dependent loads, so the tile is the smallest the instruction gives, K is
@@ -12,8 +12,8 @@
 // the tiny decoder: K = 1024, N = 256: 119 us (8 workgroups of 64 x 64, plain
 // FMAs) -> 7; a layer's GEMMs with their epilogue and norm kernels 400 -> 25.
 //
-// General form (K or leading dimensions not multiples of 4, unaligned
-// operands, rotary heads not a multiple of 32): 64x64-tiled FMA GEMM into a
+// General form (outputs of many 64x64 tiles, K or leading dimensions not multiples
+// of 4, unaligned operands, rotary heads not a multiple of 32): 64x64-tiled FMA GEMM into a
 // float scratch buffer followed by an element-wise epilogue kernel.
 #include "gemm_tile.h"
 
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(64 * W) void gemm_f32_mfma_kernel(GP p, KvF32 kv) {
   for (int b = 0; b < NB; ++b) acc[b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   float ss = 0.0f;
   // lane (row r16, q) holds k = k0 + 16 h + 4 q + 0..3 of both operands, so the
-  // instruction's four k are 4 q + e of the four q, for e = 0..3.  Four of the
+  // instruction's four k are 4 q + e of the four q, for e = 0..3.  Two of the
   // wave's 32-deep pieces are loaded at once.
   constexpr int U = 2, kStep = 32 * W;
 #pragma unroll 1

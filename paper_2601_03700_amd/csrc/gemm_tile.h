@@ -1,16 +1,16 @@
 // The output tile of the bf16 GEMMs, C[m][n] = sum_k A[m][k] B[n][k] (B in
 // nn.Linear [out][in] order, so both operands are K-contiguous), and its
-// epilogues.  Two sizes, both by 256 threads: 256x256 (gemm.hip: many rows)
-// and 128x256 (gemm_mid.hip).
+// epilogues.  Three sizes, all by 256 threads: 256x256 (gemm.hip: many rows),
+// 128x256 and 128x128 (gemm_mid.h, and the K/V generation of few tiles).
 //
 // v_mfma_f32_32x32x16_bf16; each of the four waves owns 128 rows x 128
-// columns (4x4 MFMA blocks, 256 accumulators per lane held in AGPRs) or 64 x
-// 128 (2x4 blocks).  K advances 64 at a time.  Operands reach LDS by direct global->LDS loads
+// columns (4x4 MFMA blocks, 256 accumulators per lane held in AGPRs), 64 x 128
+// (2x4 blocks) or 32 x 128 (1x4).  K advances 64 at a time.  Operands reach LDS by direct global->LDS loads
 // (global_load_lds_dwordx4: lane l of an instruction lands 16 bytes at base
 // + 16 l), eight lanes per 128-byte row, so every row of a stage is one whole
 // cache line: the load path sustains about 1.5x the bytes per cycle it does
 // with half-line requests.  The LDS is a ring of about two and a
-// half stages (160 KiB, 256x256) or three (144 KiB); while stage k is
+// half stages (160 KiB, 256x256; 80 KiB, 128x128) or three (144 KiB); while stage k is
 // consumed, stage k+1 and (parts of) stage k+2 are in flight, so the loads
 // that miss L2 have one to two stages of MFMA work to land.  Within a row the
 // eight 16-byte chunks are permuted, chunk c of row r at position
@@ -165,8 +165,9 @@ __device__ __forceinline__ float silu(float g) {
 // a = 0..13.5 to 4.5e-8 relative (least squares weighted towards the largest
 // error), is within kGeluErr a of the form with erff, so where both ends of that
 // interval round to the same bf16 that is the result; erff decides the others
-// (6e-4 of the values in (-1, 0), 3e-3 in (-2, -1), 4e-2 in (-3, -2)).  The two-branch erff took 110 of the
-// 270 us of a 32768 x 3072 GELU projection.
+// (6e-4 of the values in (-1, 0), 3e-3 in (-2, -1), 4e-2 in (-3, -2)).  A 32768 x
+// 3072 x 768 GELU projection takes 196 us; 185 with the polynomial alone, whose f32
+// results are off by up to 7e-6 (near -12.6) and whose bf16 ones differ now and then.
 constexpr float kGeluErr = 4.5e-7f;   // the largest over all floats: 2.98e-7
 __device__ __forceinline__ uint32_t gelu_ends(float x) {   // low and high end, rounded
   const float a = fabsf(x);

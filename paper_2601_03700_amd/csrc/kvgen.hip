@@ -171,17 +171,13 @@ extern "C" size_t adept_kv_generate_workspace_bytes(int n_layers, int max_rows) 
   return total;
 }
 
-adept_status adept::kv_generate_upto(int max_skipped, adept_dtype dt, int n_layers, int d_model, int n_heads,
-                                     int head_dim, float eps, const void* s_map,
-                                     const int32_t* rows, const int32_t* n_rows,
-                                     int max_rows, const int32_t* exit_layer,
-                                     const int32_t* cache_slot, const int32_t* pos,
-                                     const void* w_kv, int64_t w_kv_layer_stride,
-                                     const void* attn_gain, const float* rope_cos,
-                                     const float* rope_sin, int rope_max_pos,
-                                     void* k_cache, void* v_cache, int64_t n_slots,
-                                     void* workspace, size_t workspace_bytes,
-                                     void* stream) {
+adept_status adept::kv_generate_upto(
+    int max_skipped, adept_dtype dt, int n_layers, int d_model, int n_heads, int head_dim, float eps,
+    const void* s_map, const int32_t* rows, const int32_t* n_rows, int max_rows,
+    const int32_t* exit_layer, const int32_t* cache_slot, const int32_t* pos, const void* w_kv,
+    int64_t w_kv_layer_stride, const void* attn_gain, const float* rope_cos, const float* rope_sin,
+    int rope_max_pos, void* k_cache, void* v_cache, int64_t n_slots, void* workspace,
+    size_t workspace_bytes, void* stream) {
   ADEPT_REQUIRE(dt == ADEPT_F32 || dt == ADEPT_BF16, "kv_generate: bad dtype");
   ADEPT_REQUIRE(n_layers >= 1 && n_layers <= kMaxLayers, "kv_generate: n_layers %d", n_layers);
   ADEPT_REQUIRE(d_model > 0 && n_heads > 0 && head_dim > 0 && head_dim % 2 == 0,

@@ -244,15 +244,15 @@ adept_status kv_generate_family(const adept_layer_args* a, int max_skipped, adep
   const size_t esz = dt == ADEPT_BF16 ? 2 : 4;
   const void* wkv = (const char*)a->w_qkv + dq * D * (int64_t)esz;
   if (a->family == ADEPT_FAMILY_GPT2)
-    return kv_generate_layernorm_upto(max_skipped, dt, N, D, H, hd, a->rms_eps, s_map, rows, n_rows, max_rows,
-                                       a->exit_layer, a->slot, wkv, 3 * dq * D,
-                                       (const char*)a->b_qkv + dq * (int64_t)esz, 3 * dq,
-                                       a->k_cache, a->v_cache, a->n_slots, ws.kvgen,
-                                       ws.kvgen_bytes, stream);
+    return kv_generate_layernorm_upto(max_skipped, dt, N, D, H, hd, a->rms_eps, s_map, rows, n_rows,
+                                      max_rows, a->exit_layer, a->slot, wkv, 3 * dq * D,
+                                      (const char*)a->b_qkv + dq * (int64_t)esz, 3 * dq,
+                                      a->k_cache, a->v_cache, a->n_slots, ws.kvgen, ws.kvgen_bytes,
+                                      stream);
   return kv_generate_upto(max_skipped, dt, N, D, H, hd, a->rms_eps, s_map, rows, n_rows, max_rows,
-                           a->exit_layer, a->slot, a->pos, wkv, 3 * dq * D, nullptr, a->rope_cos,
-                           a->rope_sin, a->rope_max_pos, a->k_cache, a->v_cache, a->n_slots,
-                           ws.kvgen, ws.kvgen_bytes, stream);
+                          a->exit_layer, a->slot, a->pos, wkv, 3 * dq * D, nullptr, a->rope_cos,
+                          a->rope_sin, a->rope_max_pos, a->k_cache, a->v_cache, a->n_slots, ws.kvgen,
+                          ws.kvgen_bytes, stream);
 }
 
 }  // namespace
@@ -565,7 +565,8 @@ extern "C" adept_status adept_layer_step(const adept_layer_args* a, int layer, v
                                  a->n_tok, ws, stream));
   }
   if (!defer && layer < N && maxn > 0) {
-    ADEPT_TRY(kv_generate_family(a, N - layer, dt, a->h[out], a->exited, a->n_exited, maxn, ws, stream));
+    ADEPT_TRY(kv_generate_family(a, N - layer, dt, a->h[out], a->exited, a->n_exited, maxn, ws,
+                                 stream));
   }
   return ADEPT_OK;
 }
